@@ -95,7 +95,7 @@ size_t shtn_plan_device_bytes(shtn_plan_t plan);
 int shtn_plan_upload(shtn_plan_t plan, void* dev_buf, void* stream);
 
 /* Device workspace bytes needed by a transform of `nfields` fields (the
- * longitude-Fourier coefficients F_m(theta_i) and the rescaled spectrum). */
+ * longitude-Fourier coefficients F_m(theta_i), and room for a spectrum). */
 size_t shtn_work_bytes(shtn_plan_t plan, int nfields);
 
 /* Synthesis (Sec. 2.2): grid = S Q.
@@ -166,9 +166,10 @@ long shtn_plan_table(shtn_plan_t plan, int which, void* dst, size_t bytes);
  * ceil(nlat/2); built combinations: waves 1 with lp 1-8, 2 with lp 2-8, 4
  * with lp 4 or 8); fields per synthesis wave fw (1, 2, 4; fw = 4 needs
  * synth_lp <= 2); the analysis takes min(fw, 2) fields per wave when
- * analys_lp <= 4 and analys_waves <= 2, else 1; m_pairing (synthesis: 0 one
- * workgroup per order, 1 orders m and mmax-m share a workgroup so that all
- * workgroups carry equal work); split (analysis n-range piece length, a
+ * analys_lp <= 4 and analys_waves <= 2, else 1 (a plan that was never given a
+ * tiling reports fw 1 and chooses the fields per synthesis wave for each
+ * call); m_pairing (synthesis units: 0 longest first, 1 long and short units
+ * alternating); split (analysis n-range piece length, a
  * multiple of 32; 0 = automatic); fft_rows (latitude rows per FFT workgroup,
  * 0 = as many as fit).  Rebuilds the unit lists and restart tables:
  * re-upload afterwards.  Returns SHTN_EINVAL for unsupported values. */
@@ -361,7 +362,9 @@ int shtn_batch_analys(shtn_batch_t batch, const double* gridpacked, double* Qpac
  * synthesis units in longest-first order, or long and short units
  * alternating; analys_merge (0, 1): 0 launches the Legendre analysis once per
  * latitude-pair class (64, 128, 256, 512 pairs), 1 launches it once with the
- * largest class.  Re-upload afterwards. */
+ * largest class.  A batch that was never given a tiling reports {1, 1, 0, 0}
+ * and chooses the fields per synthesis wave by itself.  Re-upload
+ * afterwards. */
 int shtn_batch_set_tiling(shtn_batch_t batch, int synth_lp, int fw, int m_pairing, int analys_merge);
 /* tiling4 = {synth_lp, fw, m_pairing, analys_merge}. */
 int shtn_batch_get_tiling(shtn_batch_t batch, int* tiling4);
@@ -403,7 +406,7 @@ int shtn_batch_tune(shtn_batch_t batch, const double* Qpacked, double* gridpacke
  * HIP events recorded on the launch stream.  shtn_profile_read waits for the
  * recorded events and returns, for one kernel kind, the summed duration in
  * milliseconds and the number of launches since the last reset.  Kinds:
- * 0 spectrum rescale, 1 Legendre synthesis, 2 Legendre analysis,
+ * 0 (no kernel), 1 Legendre synthesis, 2 Legendre analysis,
  * 3 Fourier synthesis (c2r), 4 Fourier analysis (r2c).  Not for use under
  * stream capture.  shtn_profile_select restricts the timing to the kinds
  * whose bit is set in kind_mask (all kinds by default): every event pair

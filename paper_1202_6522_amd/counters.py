@@ -34,7 +34,6 @@ KERNELS = {
     "shtn::k_legendre_analys": ("legendre_analys", "legendre.hip"),
     "shtn::k_c2r": ("c2r", "fft.hip"),
     "shtn::k_r2c": ("r2c", "fft.hip"),
-    "shtn::k_prescale": ("prescale", "legendre.hip"),
 }
 
 

@@ -111,9 +111,8 @@ int sp_args(const Plan& p, const double* in, double* out, int nfields, int adjoi
 }
 
 // Legendre synthesis-type stage (synthesis or adjoint of the analysis):
-// spectra Q -> longitude coefficients F.  Qs is the scratch of the rescaled
-// spectra (on-the-fly algorithm), nfields x nlm complex plus padding.
-int leg_to_f(const Plan& p, const double* Q, double* F, double* Qs, int nfields, int adjoint, void* stream)
+// spectra Q -> longitude coefficients F.
+int leg_to_f(const Plan& p, const double* Q, double* F, int nfields, int adjoint, void* stream)
 {
     int e;
     if (stored_synth(p.algo)) {
@@ -127,23 +126,17 @@ int leg_to_f(const Plan& p, const double* Q, double* F, double* Qs, int nfields,
         if (e) return hip_fail(e, "stored-P synthesis launch");
         return SHTN_OK;
     }
-    {
-        ProfScope ps(PK_PRESCALE, stream);
-        e = launch_prescale(dplan(p), nullptr, nullptr, nullptr, Q, Qs, p.nlm, nfields, stream);
-    }
-    if (e) return hip_fail(e, "prescale launch");
     LegLaunch l{};
     l.plans = dplan(p);
     l.units = dev_table_int(p, TB_SYNTH_UNITS);
     l.nunits = (int)(p.synth_units.size() / kUnitInts);
-    l.grid_y = (nfields + p.tiling.fw - 1) / p.tiling.fw;
-    l.in = Qs;
+    l.fw = p.tiling.auto_fw ? synth_fw(nfields, l.nunits, p.tiling.synth_lp) : p.tiling.fw;
+    l.grid_y = (nfields + l.fw - 1) / l.fw;
+    l.in = Q;
     l.out = F;
     l.nfields = nfields;
     l.adjoint = adjoint;
     l.lp = p.tiling.synth_lp;
-    l.fw = p.tiling.fw;
-    l.wpg = p.synth_wpg;
     {
         ProfScope ps(PK_LEG_SYNTH, stream);
         e = launch_legendre_synth(l, stream);
@@ -282,10 +275,8 @@ int to_grid(shtn_plan_t plan, const double* Q, double* grid, int nfields, void* 
     int rc = check_call(plan, Q, Data::spec, grid, Data::grid, nfields, work);
     if (rc) return rc;
     const Plan& p = *plan->p;
-    WorkLayout wl = work_layout(p, nfields);
     double* F = (double*)work;
-    double* Qs = (double*)((char*)work + wl.f_bytes);
-    if ((rc = leg_to_f(p, Q, F, Qs, nfields, adjoint, stream))) return rc;
+    if ((rc = leg_to_f(p, Q, F, nfields, adjoint, stream))) return rc;
     return f_to_grid(p, F, grid, nfields, stream);
 }
 
@@ -535,6 +526,7 @@ int shtn_plan_set_tiling(shtn_plan_t plan, int synth_lp, int analys_lp, int anal
     p.tiling.analys_lp = analys_lp;
     p.tiling.analys_waves = analys_waves;
     p.tiling.fw = fw;
+    p.tiling.auto_fw = false;
     p.tiling.m_pairing = m_pairing;
     p.tiling.split = split;
     p.tiling.fft_rows = fft_rows;
@@ -618,11 +610,10 @@ int vec_to_grid(shtn_plan_t plan, const double* S, const double* T, double* Vt, 
     double* F4 = (double*)(w + v.f4);
     double* Fv = (double*)(w + v.fv);
     double* Q4 = (double*)(w + v.q4);
-    double* Qs = (double*)(w + v.qs);
     const long fs = f_layout(p.M, p.nlat).size;
     int e = launch_vec_spec_in(dplan(p), p.L, p.M, S, T, Q4, nfields, adjoint, stream);
     if (e) return hip_fail(e, "vector spectra launch");
-    if ((rc = leg_to_f(p, Q4, F4, Qs, 4 * nfields, adjoint, stream))) return rc;
+    if ((rc = leg_to_f(p, Q4, F4, 4 * nfields, adjoint, stream))) return rc;
     if ((e = launch_vec_f_out(dplan(p), fs, F4, Fv, nfields, stream))) return hip_fail(e, "vector combine launch");
     if ((rc = f_to_grid(p, Fv, Vt, nfields, stream))) return rc;
     return f_to_grid(p, Fv + 2 * (size_t)nfields * fs, Vp, nfields, stream);

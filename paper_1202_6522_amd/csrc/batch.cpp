@@ -34,6 +34,7 @@ namespace {
 struct BatchTiling {
     int synth_lp = 1;      // latitude pairs per synthesis lane (block of 64 lp pairs per wave)
     int fw = 1;            // fields per wave (fields of the same plan)
+    bool auto_fw = false;  // no tiling set yet: the synthesis takes as many as suit the batch
     int m_pairing = 0;     // synthesis unit order: 1 = long and short units alternate
     int analys_merge = 0;  // analysis: 1 = a single launch at the largest pairs-per-lane class
     int stored = 0;        // 1 = plans with a current stored-P table use the stored kernels
@@ -66,12 +67,12 @@ struct shtn_batch_s {
     size_t work_f_doubles = 0, work_total_bytes = 0;
     long max_nlm = 0;
     BatchTiling tiling;
+    int synth_fw = 1;  // fields per synthesis wave of the current unit tables
     // unit tables of the current tiling
     std::vector<int> synth_units, analys_units, rowblocks;
     // plans whose slots run the stored-P kernels: {plan index, first slot, slots}
     std::vector<std::array<int, 3>> stored_runs;
     std::vector<AnalysClass> classes;
-    int synth_wpg = 1;
     int fft_points = 1;  // most complex points in one FFT row block
     int fft_kmax = 1;  // longest FFT rows of the batch (sizes the FFT's LDS)
     // device image
@@ -134,51 +135,73 @@ void build_tables(shtn_batch_s& b, const BatchTiling& t)
         }
 
     // ---- synthesis units ----
-    struct SU {
+    // (the latitude blocks of one order and field group go to the XCD with the
+    // least work so far, largest first, and share its L2)
+    struct OrderUnits {
         long cost;
-        int u[kUnitInts];
+        std::vector<SynthUnit> u;
     };
-    std::vector<SU> su;
-    int maxblk = 1;
+    std::vector<OrderUnits> ou;
+    b.synth_fw = t.fw;
+    if (t.auto_fw) {
+        // one count for the launch: the cheapest over the batch's fields
+        // (work of a field: the cube of its truncation)
+        double best = 0.0;
+        for (int fw = 1; fw <= kMaxFw; fw *= 2) {
+            double c = 0.0, waves = 0.0;
+            for (size_t pi = 0; pi < b.plans.size(); pi++) {
+                const Plan& p = *b.plans[pi];
+                const int n = std::max(0, range[pi].second - range[pi].first);
+                c += (double)synth_step_cost(n, fw) * p.nlm * p.npair;
+                waves += (double)((n + fw - 1) / fw) * (p.M + 1) * ((p.npair + 63) / 64);
+            }
+            if (fw == 1 || (c <= best && waves >= 3072.0)) {
+                best = c;
+                b.synth_fw = fw;
+            }
+        }
+    }
+    const int sfw = b.synth_fw;
     for (size_t pi = 0; pi < b.plans.size(); pi++) {
         if (stored[pi]) continue;
         const Plan& p = *b.plans[pi];
         const int blk = 64 * t.synth_lp;
         const int nblk = (p.npair + blk - 1) / blk;
-        maxblk = std::max(maxblk, nblk);
-        for (int fg = range[pi].first; fg < range[pi].second; fg += t.fw) {
-            const int nf = std::min(t.fw, range[pi].second - fg);
+        for (int fg = range[pi].first; fg < range[pi].second; fg += sfw) {
+            const int nf = std::min(sfw, range[pi].second - fg);
             for (int m = 0; m <= p.M; m++) {
                 const int nj = p.L - m + 1;
+                OrderUnits o{0, {}};
                 for (int k = 0; k < nblk; k++) {
                     int jmin, jmax;
-                    SU x{0, {fg, nf, (int)pi, m, 0, 0, k * blk, 0, -1, 0, 0, 0}};
+                    SynthUnit x{{fg, nf, (int)pi, m, 0, 0, k * blk, 0, -1, 0, 0, 0}, 0};
                     if (start_range(p, m, k * blk, std::min((k + 1) * blk, p.npair), 0, nj, jmin, jmax)) {
                         x.u[U_JS] = jmin;
                         x.u[U_JW] = jmax;
-                        x.cost = (long)(nj - jmin) * t.synth_lp * nf;
+                        x.cost = nj - jmin;
                     } else {
                         x.u[U_ZERO] = 1;
                     }
-                    su.push_back(x);
+                    o.cost += x.cost;
+                    o.u.push_back(x);
                 }
+                ou.push_back(std::move(o));
             }
         }
     }
-    // longest first; with m_pairing, long and short units alternate instead
-    std::stable_sort(su.begin(), su.end(), [](const SU& a, const SU& c) { return a.cost > c.cost; });
-    if (t.m_pairing) {
-        std::vector<SU> alt;
-        alt.reserve(su.size());
-        for (size_t lo = 0, hi = su.size(); lo < hi;) {
-            alt.push_back(su[lo++]);
-            if (lo < hi) alt.push_back(su[--hi]);
+    std::stable_sort(ou.begin(), ou.end(), [](const OrderUnits& a, const OrderUnits& c) { return a.cost > c.cost; });
+    {
+        std::vector<SynthUnit> sq[kXcds];
+        long load[kXcds] = {0};
+        for (auto& o : ou) {
+            int x = 0;
+            for (int k = 1; k < kXcds; k++)
+                if (load[k] < load[x]) x = k;
+            load[x] += o.cost;
+            sq[x].insert(sq[x].end(), o.u.begin(), o.u.end());
         }
-        su.swap(alt);
+        pack_synth_queues(sq, t.m_pairing, b.synth_units);
     }
-    b.synth_units.clear();
-    for (auto& x : su) b.synth_units.insert(b.synth_units.end(), x.u, x.u + kUnitInts);
-    b.synth_wpg = std::min(t.synth_lp == 1 && t.fw == 1 ? 16 : 8, maxblk);
 
     // ---- analysis units, per (pairs per lane, waves) class ----
     int cls_max = 0, npair_max = 0;
@@ -202,6 +225,10 @@ void build_tables(shtn_batch_s& b, const BatchTiling& t)
     for (int cl : classes) {
         const int lp = cl / 16, waves = cl % 16;
         const int fw = analys_fw(t.fw, lp, waves);
+        struct SU {
+            long cost;
+            int u[kUnitInts];
+        };
         std::vector<SU> au;
         for (size_t pi = 0; pi < b.plans.size(); pi++) {
             const Plan& p = *b.plans[pi];
@@ -341,29 +368,21 @@ int run_synth(const shtn_batch_s& b, const double* Q, double* grid, void* work, 
 {
     const int ns = (int)b.slot_field.size();
     double* F = (double*)work;
-    double* Qs = F + b.work_f_doubles;
     const DevPlan* plans = dev_at<const DevPlan>(b, b.off_plans);
     int e;
-    {
-        ProfScope ps(PK_PRESCALE, stream);
-        e = launch_prescale(plans, dev_at<const long>(b, b.off_q), dev_at<const long>(b, b.off_s),
-                            dev_at<const int>(b, b.off_slot_plan), Q, Qs, b.max_nlm, ns, stream);
-    }
-    if (e) return hip_error(e, "batch prescale launch");
     LegLaunch l{};
     l.plans = plans;
     l.units = dev_at<const int>(b, b.off_su);
     l.nunits = (int)(b.synth_units.size() / kUnitInts);
     l.grid_y = 1;
-    l.q_off = dev_at<const long>(b, b.off_s);
+    l.q_off = dev_at<const long>(b, b.off_q);
     l.f_off = dev_at<const long>(b, b.off_f);
-    l.in = Qs;
+    l.in = Q;
     l.out = F;
     l.nfields = ns;
     l.adjoint = 0;
     l.lp = b.tiling.synth_lp;
-    l.fw = b.tiling.fw;
-    l.wpg = b.synth_wpg;
+    l.fw = b.synth_fw;
     {
         ProfScope ps(PK_LEG_SYNTH, stream);
         e = launch_legendre_synth(l, stream);
@@ -646,8 +665,11 @@ shtn_batch_t shtn_batch(int nfields, const shtn_plan_t* plans)
         BatchTiling worst;
         build_tables(*b, worst);
         b->max_image = b->image.size();
+        b->tiling.auto_fw = true;
         build_tables(*b, b->tiling);
-        b->max_image = std::max(b->max_image, b->image.size());
+        // (the padding of the queues differs between tilings by less than an
+        // order's blocks per XCD)
+        b->max_image = std::max(b->max_image, b->image.size()) + kXcds * 64 * kUnitInts * sizeof(int);
         return b;
     } catch (const std::bad_alloc&) {
         set_error(SHTN_ENOMEM, "out of host memory");
@@ -705,7 +727,7 @@ int shtn_batch_analys(shtn_batch_t batch, const double* gridpacked, double* Qpac
 int shtn_batch_set_tiling(shtn_batch_t batch, int synth_lp, int fw, int m_pairing, int analys_merge)
 {
     if (!batch) return set_error(SHTN_EINVAL, "null batch");
-    BatchTiling t{synth_lp, fw, m_pairing, analys_merge, batch->tiling.stored};
+    BatchTiling t{synth_lp, fw, false, m_pairing, analys_merge, batch->tiling.stored};
     int rc = validate(t);
     if (rc) return rc;
     try {
@@ -801,7 +823,7 @@ int shtn_batch_tune(shtn_batch_t batch, const double* Qpacked, double* gridpacke
             for (int lp : {1, 2})
                 for (int fw : {1, 2, 4})
                     for (int mp : {0, 1})
-                        for (int merge : {0, 1}) cands.push_back(BatchTiling{lp, fw, mp, merge, st});
+                        for (int merge : {0, 1}) cands.push_back(BatchTiling{lp, fw, false, mp, merge, st});
         for (const BatchTiling& t : cands) {
             build_tables(b, t);
             b.tiling = t;

@@ -11,14 +11,13 @@
 //
 // The recurrence runs in the rescaled form u_n = x u_{n-1} + beta_n u_{n-2}
 // (two FP64 operations per step: one multiply by an SGPR coefficient and one
-// FMA), with P_n^m = gamma_n u_n; gamma is folded into the spectrum before the
-// synthesis and applied after the reduction in the analysis.  Recurrence
-// coefficients and spectra are wave-uniform and are read with scalar loads
-// into SGPRs, in blocks of several degrees, so every lane's FMAs take them as
-// operands for free.  The tables are padded past their last entry so a block
-// load at the end of an order stays in bounds.
+// FMA), with P_n^m = gamma_n u_n; gamma is folded into the spectrum as the
+// synthesis loads it and applied after the reduction in the analysis.
+// Recurrence coefficients are wave-uniform and are read with scalar loads into
+// SGPRs, in blocks of several degrees; their table is padded past its last
+// entry so a block load at the end of an order stays in bounds.
 //
-// One work unit = one wave of 64 lanes, LP latitude pairs per lane and FW
+// One synthesis unit = one wave of 64 lanes, LP latitude pairs per lane and FW
 // fields that share the plan.
 #include <hip/hip_runtime.h>
 
@@ -30,6 +29,24 @@ typedef const __attribute__((address_space(4))) double* cdp;
 typedef const __attribute__((address_space(4))) int* cip;
 typedef const __attribute__((address_space(4))) long* clp;
 typedef const __attribute__((address_space(4))) DevPlan* cplan;
+typedef const __attribute__((address_space(1))) char* gcp;
+
+// Loads at a 32-bit byte offset from a wave-uniform base.
+__device__ __forceinline__ double ld1(gcp base, unsigned off)
+{
+    return *(const __attribute__((address_space(1))) double*)(base + off);
+}
+__device__ __forceinline__ double2 ld2(gcp base, unsigned off)
+{
+    const __attribute__((address_space(1))) double* p = (const __attribute__((address_space(1))) double*)(base + off);
+    return make_double2(p[0], p[1]);
+}
+
+// A block of wave-uniform scalar operands.
+template <int N>
+struct DN {
+    double v[N];
+};
 
 struct LegArgs {
     const DevPlan* plans;
@@ -41,7 +58,9 @@ struct LegArgs {
     int nfields;
     int adjoint;
     int nunits;
-    int wpg;  // waves (units) per workgroup
+    // synthesis: field groups (of FW fields) of this launch, and the first one
+    int groups, group0;
+    int waves;  // synthesis: waves per workgroup
 };
 
 __device__ __forceinline__ long field_q_off(const LegArgs& a, int f, long nlm)
@@ -55,79 +74,8 @@ __device__ __forceinline__ long field_f_off(const LegArgs& a, int f, long fsize)
 }
 
 // ---------------------------------------------------------------------------
-// Spectrum rescaling: Qs = gamma * Q (complex), per field.
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-k_prescale(const DevPlan* plans, const long* q_off, const long* s_off, const int* fplan,
-           const double* Q, double* Qs, int nfields)
-{
-    const int f = blockIdx.y;
-    if (f >= nfields) return;
-    const int pi = fplan ? fplan[f] : 0;
-    const DevPlan& P = plans[pi];
-    const long qo = q_off ? q_off[f] : (long)f * 2 * P.nlm;
-    const long so = s_off ? s_off[f] : (long)f * 2 * P.nlm;
-    // two coefficients per thread, both loads issued before the stores
-    const long i0 = (long)blockIdx.x * (2 * blockDim.x) + threadIdx.x;
-    const long i1 = i0 + blockDim.x;
-    const bool v0 = i0 < P.nlm, v1 = i1 < P.nlm;
-    double g0 = 0.0, g1 = 0.0;
-    double2 q0 = make_double2(0.0, 0.0), q1 = q0;
-    if (v0) { g0 = P.gamma[i0]; q0 = *(const double2*)(Q + qo + 2 * i0); }
-    if (v1) { g1 = P.gamma[i1]; q1 = *(const double2*)(Q + qo + 2 * i1); }
-    if (v0) *(double2*)(Qs + so + 2 * i0) = make_double2(g0 * q0.x, g0 * q0.y);
-    if (v1) *(double2*)(Qs + so + 2 * i1) = make_double2(g1 * q1.x, g1 * q1.y);
-}
-
-// Per-lane vector loads that warm L2 ahead of the scalar loads (synthesis).
-constexpr int kPrefetchSlots = 2;
-
-// Blocks of scalar operands.
-template <int N>
-struct DN {
-    double v[N];
-};
-
-// ---------------------------------------------------------------------------
 // Lane starts (shared by both directions).
 // ---------------------------------------------------------------------------
-// Per lane and pair: the step at which the lane starts and the state
-// (u_{j-2}, u_{j-1}) entering it; before that step the lane holds 0.
-template <int LP>
-struct Starts {
-    int j[LP];
-    double ya[LP], yb[LP];
-};
-
-template <int LP>
-__device__ __forceinline__ void load_starts(Starts<LP>& st, cplan P, int m, int pb, int nj)
-{
-    const int lane = threadIdx.x & 63;
-    const int npair = P->npair;
-#pragma unroll
-    for (int p = 0; p < LP; p++) {
-        const int pair = pb + p * 64 + lane;
-        const bool act = pair < npair;
-        const size_t q = (size_t)m * npair + (act ? pair : 0);
-        const double2 y = *(const double2*)(P->inj_y + 2 * q);
-        st.j[p] = act ? P->inj_j[q] : nj;
-        st.ya[p] = y.x;
-        st.yb[p] = y.y;
-    }
-}
-
-// Lanes whose start step is j take their stored state (a select per state).
-template <int LP>
-__device__ __forceinline__ void start_lanes(double (&ua)[LP], double (&ub)[LP], const Starts<LP>& st, int j)
-{
-#pragma unroll
-    for (int p = 0; p < LP; p++) {
-        const bool go = st.j[p] == j;
-        ua[p] = go ? st.ya[p] : ua[p];
-        ub[p] = go ? st.yb[p] : ub[p];
-    }
-}
-
 // Analysis: the start steps stay in registers and the stored states in this
 // lane's slots in LDS (read back only at the checkpoints of the start
 // window, so they hold no registers through the degree loop).
@@ -157,6 +105,20 @@ __device__ __forceinline__ void rescale(double (&ua)[LP], double (&ub)[LP], int 
 
 // ---------------------------------------------------------------------------
 // Synthesis: F_m(theta) for one order, LP pairs per lane, FW fields.
+//
+// Bound by the FP64 VALU, whose clock the chip's power holds to about 2.0-2.2
+// GHz under this load: 2 + 2 FW instructions per degree and pair.  What kept
+// the kernel from that rate was the feeding of the coefficients (as scalar
+// loads they shared a small cache, so eight waves of one order had to run in
+// one workgroup, and several fields per wave gained nothing) and the uneven
+// sum of the waves a SIMD was dealt.  Here the 16 lanes of every row of a wave
+// hold the coefficients of 16 degrees, loaded as one vector, and each FMA
+// picks its degree by a row broadcast of its operand.  A wave then depends on
+// no other, and units can be placed freely (synth_unit).  Measured (library
+// events, us, before and after): lmax 1023, one field, 49.7 -> 41.6 (and the
+// launch that multiplied the spectrum by gamma, 5.7, is gone), four fields
+// 167.9 -> 90.2; lmax 2047 276.5 -> 235.5; lmax 511, 16 fields, 103.8 -> 55.6;
+// lmax 255 12.5 -> 10.2.
 // ---------------------------------------------------------------------------
 template <int LP, int FW>
 struct SynthState {
@@ -164,127 +126,128 @@ struct SynthState {
     double er[LP][FW], ei[LP][FW], orr[LP][FW], oi[LP][FW];
 };
 
-// Degrees per block of scalar operands: four, two with four fields, so that
-// a block (beta and the spectra of all fields) fits the scalar registers.
-// Blocks start at even offsets and hold an even number of steps, so a step's
-// parity within its block is the parity of its degree offset.
-template <int FW>
-constexpr int block_steps() { return FW >= 4 ? 2 : 4; }
+// Degrees per group of coefficients: the 16 lanes of each row of a wave hold
+// the coefficients of 16 consecutive degrees.
+constexpr int kGroup = 16;
 
-// beta and the rescaled spectrum (re, im per field) for NS = block_steps degrees
-template <int FW>
-struct SBlock {
-    static constexpr int NS = block_steps<FW>();
-    static_assert(NS % 2 == 0, "blocks keep the step parity");
-    DN<NS> b;
-    DN<2 * NS> q[FW];
-};
-
-template <int FW>
-__device__ __forceinline__ void load_block(SBlock<FW>& B, cdp bet, const cdp (&qs)[FW], int j)
+// acc += c(lane T of the reader's row of 16 lanes) * u: the coefficient is
+// broadcast by the operand's own lane select (DPP row_newbcast), which the
+// compiler does not form by itself for FP64.  c must have been written by a
+// load or at least two instructions earlier (ready_for_dpp).
+template <int T>
+__device__ __forceinline__ void fmac_row(double& acc, double c, double u)
 {
-    constexpr int NS = SBlock<FW>::NS;
-    typedef const __attribute__((address_space(4))) DN<NS>* cbp;
-    typedef const __attribute__((address_space(4))) DN<2 * NS>* cqp;
-    cbp pb = (cbp)(bet + j);
-#pragma unroll
-    for (int i = 0; i < NS; i++) B.b.v[i] = pb->v[i];
-#pragma unroll
-    for (int f = 0; f < FW; f++) {
-        cqp pq = (cqp)(qs[f] + 2 * j);
-#pragma unroll
-        for (int i = 0; i < 2 * NS; i++) B.q[f].v[i] = pq->v[i];
-    }
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(c), "v"(u), "n"(T));
 }
 
-// Step t of a block (degree offset j + t, j even).  Even t advance ua and
-// feed the even (E) sums, odd t advance ub and feed the odd (O) sums.
-template <int LP, int FW>
-__device__ __forceinline__ void synth_step(SynthState<LP, FW>& s, const SBlock<FW>& B, int t)
+// Two wait states between the instructions that wrote these registers and
+// their first use as a broadcast operand.
+template <int FW>
+__device__ __forceinline__ void ready_for_dpp(double2 (&q)[FW])
 {
-    const double b = B.b.v[t];
-    if ((t & 1) == 0) {
+    if constexpr (FW == 1)
+        asm volatile("s_nop 1" : "+v"(q[0].x), "+v"(q[0].y));
+    else if constexpr (FW == 2)
+        asm volatile("s_nop 1" : "+v"(q[0].x), "+v"(q[0].y), "+v"(q[1].x), "+v"(q[1].y));
+    else
+        asm volatile("s_nop 1"
+                     : "+v"(q[0].x), "+v"(q[0].y), "+v"(q[1].x), "+v"(q[1].y), "+v"(q[2].x), "+v"(q[2].y),
+                       "+v"(q[3].x), "+v"(q[3].y));
+}
+
+// Keeps a uniform branch a branch (the compiler would turn a short body into
+// selects that run on every pass).
+__device__ __forceinline__ void keep_branch() { asm volatile(""); }
+
+// Step T of a group (degree offset 16 g + T).  Even T advance ua and feed the
+// even (E) sums, odd T advance ub and feed the odd (O) sums.
+template <int LP, int FW, int T>
+__device__ __forceinline__ void synth_step(SynthState<LP, FW>& s, double b, const double2 (&q)[FW])
+{
+    if constexpr (T % 2 == 0) {
 #pragma unroll
         for (int p = 0; p < LP; p++) s.ua[p] = fma(s.x[p], s.ub[p], b * s.ua[p]);
 #pragma unroll
-        for (int p = 0; p < LP; p++) {
+        for (int f = 0; f < FW; f++) {
 #pragma unroll
-            for (int f = 0; f < FW; f++) {
-                s.er[p][f] = fma(B.q[f].v[2 * t], s.ua[p], s.er[p][f]);
-                s.ei[p][f] = fma(B.q[f].v[2 * t + 1], s.ua[p], s.ei[p][f]);
+            for (int p = 0; p < LP; p++) {
+                fmac_row<T>(s.er[p][f], q[f].x, s.ua[p]);
+                fmac_row<T>(s.ei[p][f], q[f].y, s.ua[p]);
             }
         }
     } else {
 #pragma unroll
         for (int p = 0; p < LP; p++) s.ub[p] = fma(s.x[p], s.ua[p], b * s.ub[p]);
 #pragma unroll
-        for (int p = 0; p < LP; p++) {
+        for (int f = 0; f < FW; f++) {
 #pragma unroll
-            for (int f = 0; f < FW; f++) {
-                s.orr[p][f] = fma(B.q[f].v[2 * t], s.ub[p], s.orr[p][f]);
-                s.oi[p][f] = fma(B.q[f].v[2 * t + 1], s.ub[p], s.oi[p][f]);
+            for (int p = 0; p < LP; p++) {
+                fmac_row<T>(s.orr[p][f], q[f].x, s.ub[p]);
+                fmac_row<T>(s.oi[p][f], q[f].y, s.ub[p]);
             }
         }
     }
 }
 
-// The steps of one block; `lim` = number of valid steps.
-template <int LP, int FW>
-__device__ __forceinline__ void synth_block(SynthState<LP, FW>& s, const SBlock<FW>& B, int lim)
+// Steps T .. TE-1 of a group.
+template <int LP, int FW, int T, int TE>
+__device__ __forceinline__ void synth_steps(SynthState<LP, FW>& s, const double (&b)[kGroup], const double2 (&q)[FW])
 {
-#pragma unroll
-    for (int t = 0; t < SBlock<FW>::NS; t++)
-        if (t < lim) synth_step(s, B, t);
-}
-
-// Eight steps from j (bounded by nj; the operand tables are padded, so the
-// loads stay in bounds past nj).  One field: both 4-step blocks are loaded
-// before either is used; with several fields two blocks would not fit the
-// scalar registers, so each block is loaded where it is used.
-template <int LP, int FW>
-__device__ __forceinline__ void synth_block8(SynthState<LP, FW>& s, cdp bet, const cdp (&qs)[FW], int j, int nj)
-{
-    constexpr int NS = SBlock<FW>::NS;
-    if (FW == 1) {
-        SBlock<FW> b0, b1;
-        load_block(b0, bet, qs, j);
-        load_block(b1, bet, qs, j + NS);
-        if (j + 2 * NS <= nj) {
-            synth_block(s, b0, NS);
-            synth_block(s, b1, NS);
-        } else {
-            synth_block(s, b0, nj - j);
-            if (j + NS < nj) synth_block(s, b1, nj - j - NS);
-        }
-        return;
-    }
-#pragma unroll
-    for (int k = 0; k < 8; k += NS) {
-        if (j + k >= nj) break;
-        SBlock<FW> b0;
-        load_block(b0, bet, qs, j + k);
-        synth_block(s, b0, nj - j - k);
+    if constexpr (T < TE) {
+        synth_step<LP, FW, T>(s, b[T], q);
+        synth_steps<LP, FW, T + 1, TE>(s, b, q);
     }
 }
 
-// One wave per unit; a workgroup holds `wpg` consecutive units: the latitude
-// blocks of one order (they share scalar-cache lines), or of the orders m and
-// M-m together so that every workgroup carries the same work.
+// Unit and field group of a synthesis wave.  The unit list is eight queues,
+// one per XCD (entry 8 s + x is entry s of XCD x's queue), each longest first;
+// every unit runs once per field group, the groups of a unit one after
+// another.  A workgroup takes `waves` consecutive entries of its queue.
+// Small launches take one wave per workgroup, which spreads them over the
+// whole chip.  Larger ones take four: waves of nearly the same length on the
+// four SIMDs of a CU.  An XCD's workgroups go to its 32 CUs in turn, and a CU
+// holds about six of them: nearly all of a one-field call is resident at once,
+// so what a CU is dealt decides when it ends.  Every second run of 32
+// workgroups is therefore taken backwards, so that a CU gets long and short
+// units in turn.  (At lmax 1023 the work of the SIMDs then spreads by 1.2%;
+// taken forwards throughout by 16%, and the kernel ended with the busiest,
+// 45.8 us against 37.3.)
+constexpr int kSynthWaves = 4;
+constexpr int kXcdCus = 32;
+
+__device__ __forceinline__ bool synth_unit(const LegArgs& a, int wave, int& unit, int& group)
+{
+    const int x = blockIdx.x % kXcds, n = gridDim.x / kXcds;
+    int w = blockIdx.x / kXcds;
+    const int lo = w & ~(kXcdCus - 1);
+    if (a.waves > 1 && (w & kXcdCus) && lo + kXcdCus <= n) w = 2 * lo + kXcdCus - 1 - w;
+    const int p = w * a.waves + wave;
+    const int s = p / a.groups;
+    group = a.group0 + p - s * a.groups;
+    unit = s * kXcds + x;
+    return unit < a.nunits;
+}
+
+// Waves a SIMD should hold: with two pairs and four fields per lane the
+// registers are kept to 128, four waves (left alone the compiler takes 133).
 template <int LP, int FW>
-constexpr int synth_max_threads() { return LP == 1 && FW == 1 ? 1024 : 512; }
+constexpr int synth_waves() { return LP * FW == 8 ? 4 : 1; }
 
 template <int LP, int FW>
-__global__ void __launch_bounds__((synth_max_threads<LP, FW>())) k_legendre_synth(LegArgs a)
+__global__ void __launch_bounds__(64 * kSynthWaves, (synth_waves<LP, FW>())) k_legendre_synth(LegArgs a)
 {
-    // wave-uniform for the compiler, so unit data and coefficients stay in SGPRs
+    // wave-uniform for the compiler, so unit data and beta stay in SGPRs
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int unit = blockIdx.x * a.wpg + wave;
-    if (unit >= a.nunits) return;
+    int unit, group;
+    // the memory round trips of the set-up go ahead of the steps of the waves
+    // that are under way (a late wave would wait behind all of them)
+    __builtin_amdgcn_s_setprio(3);
+    if (!synth_unit(a, wave, unit, group)) return;
     cip U = (cip)a.units + (size_t)unit * kUnitInts;
     const int m = U[U_M];
     if (m < 0) return;
-    const int field0 = U[U_FIELD] + blockIdx.y * FW;
+    const int field0 = U[U_FIELD] + group * FW;
     if (field0 >= a.nfields) return;
     const int nf = min(U[U_NF], a.nfields - field0);
     cplan P = (cplan)a.plans + U[U_PLAN];
@@ -322,112 +285,130 @@ __global__ void __launch_bounds__((synth_max_threads<LP, FW>())) k_legendre_synt
     const long base = (long)m * (2 * L + 1 - m) / 2 + m;
     const int nj = L - m + 1;
     cdp bet = (cdp)P->beta + base;
-    cdp qs[FW];
-#pragma unroll
-    for (int f = 0; f < FW; f++) qs[f] = (cdp)(a.in + qoff[f]) + 2 * base;
     cip segexp = (cip)P->segexp + ((cip)P->segoff)[m];
+    // this lane's coefficient of a group: degree offset 16 g + lane % 16
+    const int lj = lane & (kGroup - 1);
+    gcp gam = (gcp)(P->gamma + base);
+    gcp qs[FW];
+#pragma unroll
+    for (int f = 0; f < FW; f++) qs[f] = (gcp)(a.in + qoff[f] + 2 * base);
 
+    // Group operands: raw coefficients and gamma of this lane's degree
+    // (clamped to the order's last), beta of the 16 degrees in SGPRs.
+    double2 qa[FW], qb[FW];
+    double ga, gb;
+    auto load_q = [&](double2 (&q)[FW], double& g, int j0) {
+        const unsigned j = (unsigned)min(j0 + lj, nj - 1);
+        g = ld1(gam, 8 * j);
+#pragma unroll
+        for (int f = 0; f < FW; f++) q[f] = ld2(qs[f], 16 * j);
+    };
+    // gamma folded in; degrees past the order's last contribute exactly 0
+    auto scale_q = [&](double2 (&q)[FW], double g, int j0) {
+#pragma unroll
+        for (int f = 0; f < FW; f++) q[f] = make_double2(g * q[f].x, g * q[f].y);
+        if (j0 + kGroup > nj) {
+            keep_branch();
+            const bool in = j0 + lj < nj;
+#pragma unroll
+            for (int f = 0; f < FW; f++) q[f] = make_double2(in ? q[f].x : 0.0, in ? q[f].y : 0.0);
+        }
+        ready_for_dpp(q);
+    };
+    double ba[kGroup], bb[kGroup];
+    auto load_b = [&](double (&b)[kGroup], int j0) {
+        typedef const __attribute__((address_space(4))) DN<kGroup>* cbp;
+        cbp pb16 = (cbp)(bet + j0);
+#pragma unroll
+        for (int i = 0; i < kGroup; i++) b[i] = pb16->v[i];
+    };
+
+    // The order runs in segments of 32 degrees: an even and an odd group.
+    // Coefficients are loaded one segment ahead, beta one group ahead (the
+    // table is padded, and no group past the order's last is loaded).
+    const int js0 = jstart & ~(kSegLen - 1);
+    load_q(qa, ga, js0);
+    load_q(qb, gb, js0 + kGroup);
+    // Lane starts: nearly every lane of a block starts at the block's first
+    // start, from the state loaded here; the few that join later (4% of the
+    // blocks at lmax 1023) load theirs when their step comes.
     SynthState<LP, FW> s;
-    Starts<LP> st;
-    load_starts(st, P, m, pb, nj);
-#pragma unroll
-    for (int p = 0; p < LP; p++) {
-        const int pair = pb + p * 64 + lane;
-        const bool act = pair < npair;
-        s.x[p] = act ? P->xp[act ? pair : 0] : 0.0;
-        s.ua[p] = 0.0;
-        s.ub[p] = 0.0;
-#pragma unroll
-        for (int f = 0; f < FW; f++) s.er[p][f] = s.ei[p][f] = s.orr[p][f] = s.oi[p][f] = 0.0;
-    }
-
-    // Warm L2 with this order's beta and spectrum from the first step on: the
-    // waves of the order's latitude blocks touch one word per 64-byte line
-    // with vector loads into registers that are consumed only after the order
-    // is done.  They are issued after the start values above have arrived and
-    // no other vector load follows before the end, so no wave waits on them
-    // (the scalar loads are counted apart).  The scalar loads then find these
-    // lines in L2.
-    __builtin_amdgcn_sched_barrier(0);
-    unsigned pf[kPrefetchSlots];
+    int sj[LP];
+    gcp inj_y = (gcp)(P->inj_y + 2 * ((size_t)m * npair));
     {
-        const int nblk_m = (npair + 64 * LP - 1) / (64 * LP);
-        const int nthr = nblk_m * 64;
-        const int gi = (pb / (64 * LP)) * 64 + lane;
-        const int nrem = nj - jstart;
-        const int lb = (nrem * 8 + 63) / 64;   // beta lines
-        const int lq = (nrem * 16 + 63) / 64;  // spectrum lines per field
-        const char* b0 = (const char*)(P->beta + base + jstart);
+        double2 y[LP];
+        gcp inj_j = (gcp)(P->inj_j + (size_t)m * npair);
+        gcp xp = (gcp)P->xp;
 #pragma unroll
-        for (int k = 0; k < kPrefetchSlots; k++) {
-            int li = gi + k * nthr;
-            const char* addr = b0;
-            if (li < lb) {
-                addr = b0 + li * 64;
-            } else {
-                li -= lb;
+        for (int p = 0; p < LP; p++) {
+            const int pair = pb + p * 64 + lane;
+            const unsigned pc = (unsigned)min(pair, npair - 1);
+            y[p] = ld2(inj_y, 16 * pc);
+            sj[p] = *(const __attribute__((address_space(1))) int*)(inj_j + 4 * pc);
+            s.x[p] = ld1(xp, 8 * pc);
+        }
+        load_b(ba, js0);
 #pragma unroll
-                for (int f = 0; f < FW; f++) {
-                    if (li >= 0 && li < lq) addr = (const char*)(a.in + qoff[f] + 2 * (base + jstart)) + li * 64;
-                    li -= lq;
-                }
-            }
-            pf[k] = *(const unsigned*)addr;
+        for (int p = 0; p < LP; p++) {
+            if (pb + p * 64 + lane >= npair) sj[p] = nj;
+            s.ua[p] = sj[p] == jstart ? y[p].x : 0.0;
+            s.ub[p] = sj[p] == jstart ? y[p].y : 0.0;
+#pragma unroll
+            for (int f = 0; f < FW; f++) s.er[p][f] = s.ei[p][f] = s.orr[p][f] = s.oi[p][f] = 0.0;
         }
     }
-
-    // Start window: blocks of kInject steps from the first start, lanes
-    // joining at block boundaries, up to the segment boundary after the last
-    // start.  (The shift is 0 off segment boundaries: an unconditional
-    // ldexp, not a branch, which the compiler would turn into selects.)
-    static_assert(kInject == 8, "the start window advances in blocks of 8 steps");
-    int j = jstart;
-    while (j < nj && (j <= jwin || j % kSegLen != 0)) {
-        rescale(s.ua, s.ub, (j > jstart && j % kSegLen == 0) ? segexp[j / kSegLen] : 0);
-        start_lanes(s.ua, s.ub, st, j);
-        synth_block8(s, bet, qs, j, nj);
-        j += 8;
-    }
-    // Every lane has started: whole segments, straight-line.  One field: the
-    // scalar operands of each 4-step block are loaded one block ahead; with
-    // several fields each block is loaded where it is used.
-    SBlock<FW> cur;
-    if (FW == 1) load_block(cur, bet, qs, j);
-    int shn = j < nj ? segexp[j / kSegLen] : 0;
-    for (int js = j; js < nj; js += kSegLen) {
-        const int je = min(js + kSegLen, nj);
-        rescale(s.ua, s.ub, shn);
-        shn = js + kSegLen < nj ? segexp[js / kSegLen + 1] : 0;
-        if (je - js == kSegLen) {
-            constexpr int NS = SBlock<FW>::NS;
-            // operands of the segment from one base pointer per table, so
-            // that the block loads take fixed offsets
-            const cdp bseg = bet + js;
-            cdp qseg[FW];
+    int shn = segexp[js0 / kSegLen];
+    auto join = [&](int j) {
 #pragma unroll
-            for (int f = 0; f < FW; f++) qseg[f] = qs[f] + 2 * js;
-#pragma unroll
-            for (int bk = 0; bk < kSegLen; bk += NS) {
-                if (FW == 1) {
-                    SBlock<FW> nxt;
-                    load_block(nxt, bseg, qseg, bk + NS);
-                    synth_block(s, cur, NS);
-                    cur = nxt;
-                } else {
-                    SBlock<FW> b0;
-                    load_block(b0, bseg, qseg, bk);
-                    synth_block(s, b0, NS);
-                }
+        for (int p = 0; p < LP; p++) {
+            const bool go = sj[p] == j;
+            if (__any(go)) {
+                const double2 y = ld2(inj_y, 16 * (unsigned)min(pb + p * 64 + lane, npair - 1));
+                s.ua[p] = go ? y.x : s.ua[p];
+                s.ub[p] = go ? y.y : s.ub[p];
+                // (used here, so that the wait for the load stays in this branch)
+                asm volatile("" : "+v"(s.ua[p]), "+v"(s.ub[p]));
             }
-        } else {
-            // last, partial segment of the order
-            for (int jj = js; jj < je; jj += 8) synth_block8(s, bet, qs, jj, nj);
         }
-    }
+    };
 
-    unsigned sink = 0;
-#pragma unroll
-    for (int k = 0; k < kPrefetchSlots; k++) sink ^= pf[k];
+    // Half a group: kInject = 8 steps, from the first start on and while the
+    // order has degrees; up to the last start, lanes join at its checkpoint.
+    static_assert(kInject == 8 && kGroup == 16, "two start checkpoints per group");
+#define SHTN_SYNTH_HALF(JH, T0, B, Q)                            \
+    if ((JH) >= jstart && (JH) < nj) {                           \
+        if ((JH) > jstart && (JH) <= jwin) {                     \
+            keep_branch();                                       \
+            join(JH);                                            \
+        }                                                        \
+        synth_steps<LP, FW, T0, T0 + 8>(s, B, Q);                \
+    }
+    __builtin_amdgcn_s_setprio(0);
+    for (int js = js0; js < nj; js += kSegLen) {
+        const int jn = js + kSegLen < nj ? js + kSegLen : js;  // next segment (or this one again: not used)
+        const int jo = js + kGroup < nj ? js + kGroup : js;    // odd group (likewise)
+        const int sh = js > jstart ? shn : 0;
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): ba and the shift
+        __builtin_amdgcn_sched_barrier(0);
+        load_b(bb, jo);
+        shn = segexp[jn / kSegLen];
+        __builtin_amdgcn_sched_barrier(0);
+        rescale(s.ua, s.ub, sh);
+        scale_q(qa, ga, js);
+        SHTN_SYNTH_HALF(js, 0, ba, qa)
+        SHTN_SYNTH_HALF(js + 8, 8, ba, qa)
+        load_q(qa, ga, jn);
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): bb
+        __builtin_amdgcn_sched_barrier(0);
+        load_b(ba, jn);
+        __builtin_amdgcn_sched_barrier(0);
+        scale_q(qb, gb, js + kGroup);
+        SHTN_SYNTH_HALF(js + 16, 0, bb, qb)
+        SHTN_SYNTH_HALF(js + 24, 8, bb, qb)
+        load_q(qb, gb, jn + kGroup);
+    }
+#undef SHTN_SYNTH_HALF
+    __builtin_amdgcn_s_setprio(3);
 
     // Mirror fold: north = E + O, south = E - O.  For the adjoint of the
     // analysis the output carries (2 pi/nphi) w_i / c_m.
@@ -449,8 +430,6 @@ __global__ void __launch_bounds__((synth_max_threads<LP, FW>())) k_legendre_synt
                                                                         sc * (s.ei[p][f] - s.oi[p][f]));
         }
     }
-    // keeps the prefetch loads alive; nfields is never negative
-    if (a.nfields < 0) a.out[lane] = (double)sink;
 }
 
 // ---------------------------------------------------------------------------
@@ -881,30 +860,29 @@ __global__ void __launch_bounds__(64 * W) k_legendre_analys(LegArgs a)
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-int launch_prescale(const DevPlan* plans, const long* q_off, const long* s_off, const int* fplan,
-                    const double* Q, double* Qs, long max_nlm, int nfields, void* stream)
-{
-    const int blocks = (int)((max_nlm + 511) / 512);
-    dim3 grid(std::max(1, blocks), nfields);
-    hipLaunchKernelGGL(k_prescale, grid, dim3(256), 0, (hipStream_t)stream, plans, q_off, s_off,
-                       fplan, Q, Qs, nfields);
-    return (int)hipGetLastError();
-}
-
 template <int LP, int FW>
 static int launch_synth_t(const LegLaunch& l, void* stream)
 {
-    const int wpg = std::max(1, std::min(l.wpg, synth_max_threads<LP, FW>() / 64));
-    LegArgs a{l.plans, l.units, l.q_off, l.f_off, l.in, l.out, l.nfields, l.adjoint, l.nunits, wpg};
-    hipLaunchKernelGGL((k_legendre_synth<LP, FW>), dim3((l.nunits + wpg - 1) / wpg, l.grid_y),
-                       dim3(64 * wpg), 0, (hipStream_t)stream, a);
+    // (a launch's threads are counted in 32 bits: one launch unless the call
+    // has far more fields than the card holds)
+    const int most = std::max(1, (1 << 25) / l.nunits);
+    for (int g0 = 0; g0 < l.grid_y; g0 += most) {
+        const int ng = std::min(most, l.grid_y - g0);
+        // two waves per SIMD or fewer: one per workgroup (lmax 255, one
+        // field: 10.2 us, with four 11.2; lmax 511: 16.2, with four 17.9)
+        const int waves = (long)l.nunits * ng > 2048 ? kSynthWaves : 1;
+        LegArgs a{l.plans, l.units, l.q_off, l.f_off, l.in, l.out, l.nfields, l.adjoint, l.nunits, ng, g0, waves};
+        const int per_xcd = (l.nunits / kXcds * ng + waves - 1) / waves;
+        hipLaunchKernelGGL((k_legendre_synth<LP, FW>), dim3(kXcds * per_xcd), dim3(64 * waves), 0,
+                           (hipStream_t)stream, a);
+    }
     return (int)hipGetLastError();
 }
 
 template <int LP, int FW, int W>
 static int launch_analys_t(const LegLaunch& l, void* stream)
 {
-    LegArgs a{l.plans, l.units, l.q_off, l.f_off, l.in, l.out, l.nfields, l.adjoint, l.nunits, 1};
+    LegArgs a{l.plans, l.units, l.q_off, l.f_off, l.in, l.out, l.nfields, l.adjoint, l.nunits, 1, 0, W};
     hipLaunchKernelGGL((k_legendre_analys<LP, FW, W>), dim3(l.nunits, l.grid_y), dim3(64 * W), 0,
                        (hipStream_t)stream, a);
     return (int)hipGetLastError();

@@ -350,9 +350,10 @@ Plan* build_plan(int L, int M, int nlat, int nphi, std::string& err)
         p->rtw[2 * m + 1] = (double)sinl(a);
     }
 
-    // default tiling: one pair per synthesis lane, orders unpaired (measured
-    // fastest at lmax 1023); one analysis wave covers every pair of its order
-    p->tiling.synth_lp = 1;
+    // default tiling: one pair per synthesis lane, two where the waves are
+    // many (lmax 1023: 41.6 us with one pair, 43.0 with two; lmax 2047: 244.0
+    // and 235.5); one analysis wave covers every pair of its order
+    p->tiling.synth_lp = (long)(M + 1) * ((np + 63) / 64) >= 24576 ? 2 : 1;
     p->tiling.m_pairing = 0;
     analys_shape(np, p->tiling.analys_lp, p->tiling.analys_waves);
     if (rebuild_units(*p, err)) { delete p; return nullptr; }
@@ -444,47 +445,57 @@ static long analys_unit_cost(const Plan& p, int m, int js, int j1)
     return cost;
 }
 
+void pack_synth_queues(std::vector<SynthUnit> (&q)[kXcds], int alternate, std::vector<int>& units)
+{
+    size_t len = 0;
+    for (auto& x : q) {
+        std::stable_sort(x.begin(), x.end(), [](const SynthUnit& a, const SynthUnit& b) { return a.cost > b.cost; });
+        if (alternate) {
+            std::vector<SynthUnit> alt;
+            for (size_t lo = 0, hi = x.size(); lo < hi;) {
+                alt.push_back(x[lo++]);
+                if (lo < hi) alt.push_back(x[--hi]);
+            }
+            x.swap(alt);
+        }
+        len = std::max(len, x.size());
+    }
+    units.clear();
+    units.reserve(len * kXcds * kUnitInts);
+    const int none[kUnitInts] = {0, 0, 0, -1, 0, 0, 0, 0, -1, 0, 0, 0};
+    for (size_t k = 0; k < len; k++)
+        for (auto& x : q) {
+            const int* u = k < x.size() ? x[k].u : none;
+            units.insert(units.end(), u, u + kUnitInts);
+        }
+}
+
 int rebuild_units(Plan& p, std::string& err)
 {
     const Tiling& t = p.tiling;
     const int np = p.npair, L = p.L, M = p.M;
+    const int nf = t.auto_fw ? kMaxFw : t.fw;  // most fields a unit may take
     // ---- synthesis units: order x latitude-pair block ----
-    // m_pairing 0: one workgroup per order (its latitude blocks);
-    // 1: orders m and M-m in the same workgroup (equal work per workgroup).
+    // The blocks of an order go to one XCD, whose L2 then holds its
+    // coefficients.
     p.synth_units.clear();
     const int blk = 64 * t.synth_lp;
     const int nblk = (np + blk - 1) / blk;
-    const int max_wpg = t.synth_lp == 1 && t.fw == 1 ? 16 : 8;
-    auto emit = [&](int m, int b) {
-        int u[kUnitInts] = {0, t.fw, 0, -1, 0, 0, b * blk, 0, -1, 0, 0, 0};
-        if (m >= 0) {
-            const int nj = L - m + 1;
+    std::vector<SynthUnit> sq[kXcds];
+    for (int m = 0; m <= M; m++)
+        for (int b = 0; b < nblk; b++) {
+            SynthUnit v{{0, nf, 0, m, 0, 0, b * blk, 0, -1, 0, 0, 0}, 0};
             int jmin, jmax;
-            u[U_M] = m;
-            if (start_range(p, m, b * blk, std::min((b + 1) * blk, np), 0, nj, jmin, jmax)) {
-                u[U_JS] = jmin;
-                u[U_JW] = jmax;
+            if (start_range(p, m, b * blk, std::min((b + 1) * blk, np), 0, L - m + 1, jmin, jmax)) {
+                v.u[U_JS] = jmin;
+                v.u[U_JW] = jmax;
+                v.cost = L - m + 1 - jmin;
             } else {
-                u[U_ZERO] = 1;  // every lane of the block is below the polar threshold
+                v.u[U_ZERO] = 1;  // every lane of the block is below the polar threshold
             }
+            sq[m % kXcds].push_back(v);
         }
-        p.synth_units.insert(p.synth_units.end(), u, u + kUnitInts);
-    };
-    if (t.m_pairing && 2 * nblk <= max_wpg) {
-        for (int m = 0; 2 * m <= M; m++) {
-            const int m2 = M - m;
-            for (int b = 0; b < nblk; b++) emit(m, b);
-            for (int b = 0; b < nblk; b++) emit(m2 != m ? m2 : -1, b);
-        }
-        p.synth_wpg = 2 * nblk;
-    } else {
-        for (int m = 0; m <= M; m++)
-            for (int b = 0; b < nblk; b++) emit(m, b);
-        // the latitude blocks of one order, or an equal share of them
-        int wpg = std::min(nblk, max_wpg);
-        while (nblk % wpg) wpg--;
-        p.synth_wpg = wpg;
-    }
+    pack_synth_queues(sq, t.m_pairing, p.synth_units);
 
     // ---- analysis units: (m, degree range) pieces of S degrees ----
     // Workgroup b runs on XCD b % kXcds.  All pieces of one order go to one
@@ -564,10 +575,10 @@ int rebuild_units(Plan& p, std::string& err)
     for (auto& q : xq) qlen = std::max(qlen, q.size());
     for (size_t k = 0; k < qlen; k++) {
         for (int x = 0; x < kXcds; x++) {
-            int u[kUnitInts] = {0, t.fw, 0, -1, 0, 0, 0, 0, -1, 0, 0, 0};
+            int u[kUnitInts] = {0, nf, 0, -1, 0, 0, 0, 0, -1, 0, 0, 0};
             if (k < xq[x].size()) {
                 const AU& a = xq[x][k];
-                const int v[kUnitInts] = {0, t.fw, 0, a.m, a.js, a.jw, a.j0, a.j1,
+                const int v[kUnitInts] = {0, nf, 0, a.m, a.js, a.jw, a.j0, a.j1,
                                           a.rst >= 0 ? rbase[a.m] + a.rst : -1, 0, 0, 0};
                 std::copy(v, v + kUnitInts, u);
             }

@@ -40,8 +40,8 @@ constexpr int kInject = 8;
 // Analysis accumulates kChunk consecutive degrees per lane before a
 // cross-lane reduction.
 constexpr int kChunk = 16;
-// Entries of zero padding after the tables that the kernels read in blocks
-// (beta, the rescaled spectrum): a block starting at an order's last degree
+// Entries of zero padding after the table that the kernels read in blocks
+// (beta): a block starting at an order's last degree
 // stays in bounds.
 constexpr int kTablePad = 32;
 // Pairs per lane and waves of an analysis unit covering npair latitude pairs
@@ -74,6 +74,13 @@ enum UnitField {
     U_ZERO = 9,   // synthesis: 1 if no lane of the block ever starts (F written as 0)
 };
 constexpr int kUnitInts = 12;
+
+// A synthesis unit and its work (steps from the first start on; 0 for a unit
+// that only writes zeros).
+struct SynthUnit {
+    int u[kUnitInts];
+    long cost;
+};
 
 // Tables of a plan's device buffer, in buffer order (Plan::table_off).
 enum DevTable {
@@ -136,8 +143,9 @@ struct Tiling {
     int synth_lp = 1;
     int analys_lp = 8;
     int analys_waves = 1;  // waves per analysis unit
-    int fw = 1;
-    int m_pairing = 0;  // synthesis: 1 = orders m and M-m share a workgroup
+    int fw = 1;         // fields per wave
+    bool auto_fw = true;  // no tiling set yet: the fields per synthesis wave are chosen per call (synth_fw)
+    int m_pairing = 0;  // synthesis: 1 = long and short units alternate in the launch order
     int split = 0;     // analysis: pieces of this many degrees, 0 = automatic
     int fft_rows = 0;  // latitude rows per FFT workgroup, 0 = automatic
 };
@@ -162,7 +170,6 @@ struct Plan {
     long nlm = 0;
     Tiling tiling;
     int split_used = 0;
-    int synth_wpg = 1;  // waves per synthesis workgroup for the unit order
     int polar_log2 = kPolarLog2;  // lanes start where |P_n^m| first reaches 2^polar_log2
     // host tables
     std::vector<double> x, w;                 // full grid
@@ -258,12 +265,16 @@ inline FLayout f_layout(int M, int nlat)
 }
 // XCDs of the chip: workgroup b of a launch runs on XCD b % kXcds.
 constexpr int kXcds = 8;
+// Unit list of a synthesis launch from one queue per XCD: each sorted longest
+// first (or, with `alternate`, long and short in turn), padded with units
+// without work to the length of the longest, entry k of XCD x at k kXcds + x.
+void pack_synth_queues(std::vector<SynthUnit> (&q)[kXcds], int alternate, std::vector<int>& units);
 size_t align256(size_t v);
 
 // Workspace layout of a plan call with nfields fields.
 struct WorkLayout {
     size_t f_bytes;   // F: nfields x f_layout().size complex
-    size_t q_bytes;   // rescaled spectrum: nfields x nlm complex
+    size_t q_bytes;   // room for nfields spectra (nlm complex each; the scalar transforms do not use it)
     size_t total;
 };
 WorkLayout work_layout(const Plan& p, int nfields);
@@ -277,12 +288,31 @@ inline int analys_fw(int fw, int lp, int waves)
     return fw >= 2 && lp <= 4 && waves <= 2 ? 2 : 1;
 }
 
+// Cost of a synthesis step of n fields, fw per wave, in FP64 instructions per
+// latitude pair: 2 for the recurrence and 2 per field (a last, partial group
+// runs all fw).
+inline long synth_step_cost(int n, int fw) { return (long)((n + fw - 1) / fw) * (2 + 2 * fw); }
+constexpr int kMaxFw = 4;
+// Fields per synthesis wave for nfields fields of nunits units each: the
+// cheapest step among the built kernels that still leaves three waves for each
+// of the 1024 SIMDs (lmax 255, 16 fields: two per wave 18.8 us, four 19.6, one
+// 21.1; lmax 511, 16 fields: 64.2, 55.6 and 84.6).
+inline int synth_fw(int nfields, int nunits, int lp)
+{
+    int best = 1;
+    for (int fw = 2; fw <= kMaxFw && fw * lp <= 8; fw *= 2)
+        if (synth_step_cost(nfields, fw) <= synth_step_cost(nfields, best) &&
+            (long)nunits * ((nfields + fw - 1) / fw) >= 3072)
+            best = fw;
+    return best;
+}
+
 // Kernel launchers (legendre.hip, fft.hip).  Return a hipError_t as int.
 struct LegLaunch {
     const DevPlan* plans;  // device array of plans
     const int* units;      // device unit array
     int nunits;
-    int grid_y;            // blockIdx.y extent (field groups), 1 for batches
+    int grid_y;            // field groups of the call, 1 for batches
     const long* q_off;     // per-field offset (doubles) of the spectrum, or null (f * 2 nlm)
     const long* f_off;     // per-field offset (doubles) of F, or null (f * 2 (M+1) nlat)
     const double* in;
@@ -291,11 +321,7 @@ struct LegLaunch {
     int adjoint;           // 0 forward transform, 1 adjoint variant
     int lp, fw;            // template selection
     int waves = 1;         // analysis: waves per unit (latitude pairs 64 lp waves)
-    int wpg;               // synthesis: waves (consecutive units) per workgroup
 };
-// Qs = gamma * Q per field; q_off/s_off/fplan per field (device) or null.
-int launch_prescale(const DevPlan* plans, const long* q_off, const long* s_off, const int* fplan,
-                    const double* Q, double* Qs, long max_nlm, int nfields, void* stream);
 // Stored-P kernels (ptable.hip).
 struct PtabArgs {
     const DevPlan* plan;
