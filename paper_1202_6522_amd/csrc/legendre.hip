@@ -73,26 +73,7 @@ __device__ __forceinline__ long field_f_off(const LegArgs& a, int f, long fsize)
     return a.f_off ? ((clp)a.f_off)[f] : (long)f * 2 * fsize;
 }
 
-// ---------------------------------------------------------------------------
-// Lane starts (shared by both directions).
-// ---------------------------------------------------------------------------
-// Analysis: the start steps stay in registers and the stored states in this
-// lane's slots in LDS (read back only at the checkpoints of the start
-// window, so they hold no registers through the degree loop).
-template <int LP>
-__device__ __forceinline__ void start_lanes_lds(double (&ua)[LP], double (&ub)[LP], const int (&sj)[LP],
-                                                const double2 (*sy)[64], int j)
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int p = 0; p < LP; p++) {
-        const double2 y = sy[p][lane];
-        const bool go = sj[p] == j;
-        ua[p] = go ? y.x : ua[p];
-        ub[p] = go ? y.y : ub[p];
-    }
-}
-
+// Segment shift of the recurrence states.
 template <int LP>
 __device__ __forceinline__ void rescale(double (&ua)[LP], double (&ub)[LP], int sh)
 {
@@ -568,19 +549,27 @@ __device__ __forceinline__ void analys_half_from(int pf, AState<LP, FW>& s, cons
 
 // Start checkpoint cc: in the slots whose block has a lane starting there
 // (bits of mk, wave-uniform), the lanes whose start step is cc take their
-// stored state (kept in this lane's slots in LDS).
+// stored state, loaded here: few units start lanes (two or three blocks per
+// unit at lmax 1023), and the states of the others are never read.
 template <int LP>
-__device__ __forceinline__ void start_slots(double (&ua)[LP], double (&ub)[LP], const int (&sj)[LP],
-                                            const double2 (*sy)[64], unsigned mk, int cc)
+__device__ __forceinline__ void start_slots(double (&ua)[LP], double (&ub)[LP], cplan P, int m, int pb, unsigned mk,
+                                            int cc)
 {
-    const int lane = threadIdx.x & 63;
+    const int npair = P->npair;
+    gcp inj_y = (gcp)(P->inj_y + 2 * ((size_t)m * npair));
+    gcp inj_j = (gcp)(P->inj_j + (size_t)m * npair);
 #pragma unroll
     for (int p = 0; p < LP; p++) {
         if (mk & (1u << p)) {
-            const double2 y = sy[p][lane];
-            const bool go = sj[p] == cc;
+            const int pair = pb + p * 64 + (threadIdx.x & 63);
+            const unsigned pc = (unsigned)min(pair, npair - 1);
+            const int sj = *(const __attribute__((address_space(1))) int*)(inj_j + 4 * pc);
+            const double2 y = ld2(inj_y, 16 * pc);
+            const bool go = pair < npair && sj == cc;
             ua[p] = go ? y.x : ua[p];
             ub[p] = go ? y.y : ub[p];
+            // (used here, so that the wait for the loads stays in this branch)
+            asm volatile("" : "+v"(ua[p]), "+v"(ub[p]));
         }
     }
 }
@@ -589,32 +578,37 @@ __device__ __forceinline__ void start_slots(double (&ua)[LP], double (&ub)[LP], 
 // each lane pair's partial sums (one row per degree and field, one column
 // per thread: real parts in even columns, imaginary parts in odd ones) go to
 // LDS, while the sums of the previous pass are read back, added over the
-// columns (2W threads per output, padded rows) and stored.  The rows live in
-// one buffer: one wave executes its LDS operations in order, so with W = 1
-// the reads of the previous pass, issued before this pass's writes, need no
-// barrier; with several waves a barrier after the reads lets every wave
-// finish reading before any wave writes, and one at the end of the pass
-// makes the rows visible.  (Two alternating buffers would save the first
-// barrier, but at W = 2 and 4 their LDS halves the workgroups a CU holds:
-// lmax 2047 and 4095 ran 14% and 33% slower that way.)
-// A workgroup of W waves covers 64 LP W latitude pairs: wave w takes pairs
-// [64 LP w, 64 LP (w + 1)), pair slot p of its lanes being the 64-pair block
-// LP w + p.  A pass runs as halves of kInject steps; each half first injects
-// the start states of the blocks with lanes starting at its checkpoint, then
-// runs only the slots from the first one whose block has started (the polar
-// optimisation of Sec. 3.1 at the granularity of 64 latitudes).
+// columns (two lanes per output, padded rows) and stored.  The rows are the
+// wave's own and lie in one buffer: one wave executes its LDS operations in
+// order, so the reads of the previous pass, issued before this pass's writes,
+// need no barrier.
+// A workgroup of W waves covers 64 LP W latitude pairs, 64 LP consecutive ones
+// per wave, pair slot p of a wave's lanes being one 64-pair block.  A pass
+// runs as halves of kInject steps; each half first injects the start states of
+// the blocks with lanes starting at its checkpoint, then runs only the slots
+// from the first one whose block has started (the polar optimisation of Sec.
+// 3.1 at the granularity of 64 latitudes).
+// With W > 1 the waves run apart for chunks of kWideChunk degrees: each puts
+// its sums in LDS, and at the end of a chunk the workgroup adds them up and
+// stores the outputs.  (With the waves in step for every pass, as before, all
+// of them took as long as the one at the equator, and the SIMD it ran on set
+// the time: lmax 4095 2,747 -> 2,407 us, lmax 2047 337 -> 323.)
+constexpr int kWideChunk = 256;
+
 template <int LP, int FW, int W>
 struct AnalysGeom {
     static constexpr int SC = kChunk / FW;  // degrees per pass
     static constexpr int NR = SC * FW;      // rows per pass
-    static constexpr int NT = 64 * W;       // threads = columns
-    static constexpr int PR = 2 * W;        // threads per output (row, component)
+    static constexpr int NT = 64;           // columns
+    static constexpr int PR = 2;            // lanes per output (row, component)
     static constexpr int NK = NT / 2 / PR;  // columns each of them adds
-    // row stride NT + 2 PR doubles: a thread's PR-wide column groups of
+    // row stride NT + 2 PR doubles: a lane's PR-wide column groups of
     // consecutive rows start 4 PR banks apart, so the 32 lanes of a half-wave
     // read distinct banks
     static constexpr int RS = NT + 2 * PR;
     static constexpr int NH = SC / kInject;  // halves per pass
+    // sums of a chunk: one per wave, degree, field and component
+    static constexpr int NA = W > 1 ? kWideChunk * FW * 2 : 1;
 };
 
 // One unit: degrees [j0, j1) of one order for all latitude pairs (the
@@ -622,17 +616,18 @@ struct AnalysGeom {
 template <int LP, int FW, int W>
 __device__ __forceinline__ void analys_unit(
     const LegArgs& a, int ui,
-    double (&red)[AnalysGeom<LP, FW, W>::NR][AnalysGeom<LP, FW, W>::RS],
-    double2 (&start_y)[W][LP][64])
+    double (&red_w)[W][AnalysGeom<LP, FW, W>::NR][AnalysGeom<LP, FW, W>::RS],
+    double (&acc)[W][AnalysGeom<LP, FW, W>::NA])
 {
     using G = AnalysGeom<LP, FW, W>;
     constexpr int SC = G::SC, NR = G::NR, NT = G::NT, PR = G::PR, NK = G::NK, RS = G::RS, NH = G::NH;
-    static_assert(2 * NR * PR == NT, "the threads cover the outputs");
+    static_assert(2 * NR * PR == NT, "the lanes cover the outputs");
     static_assert(kSegLen % SC == 0, "passes tile a segment");
     static_assert(SC % kInject == 0, "passes are whole halves");
     static_assert(kInject % 2 == 0, "halves keep the step parity");
     static_assert(LP <= 8 && LP * W <= kMaxMaskBlocks, "one mask word covers the unit's blocks");
 
+    __builtin_amdgcn_s_setprio(3);
     cip U = (cip)a.units + (size_t)ui * kUnitInts;
     const int m = U[U_M];
     if (m < 0) return;
@@ -645,7 +640,11 @@ __device__ __forceinline__ void analys_unit(
     const long nlm = P->nlm;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // which part of the latitudes a wave takes turns with the unit: the waves
+    // near the pole have less to do, and a workgroup's waves go to the SIMDs
+    // in a fixed order
+    const int wid = W > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
+    const int wv = W > 1 ? (wid + ui / kXcds) & (W - 1) : 0;
     const int pb = wv * 64 * LP;  // first latitude pair of this wave
     const int wb = wv * LP;       // its first 64-pair block
     const int j0 = U[U_PB], j1 = U[U_J1], js0 = U[U_JS], jwin = U[U_JW], rst = U[U_RST];
@@ -655,6 +654,7 @@ __device__ __forceinline__ void analys_unit(
     cip segexp = (cip)P->segexp + ((cip)P->segoff)[m];
     // per checkpoint: blocks with lanes starting there, blocks started
     cip ckm = (cip)P->ck_mask + (size_t)m * P->nck * 2;
+    double (&red)[NR][RS] = red_w[wid];
 
     long qoff[FW];
     long foff[FW];
@@ -666,7 +666,7 @@ __device__ __forceinline__ void analys_unit(
     }
 
     // degrees before the first started lane: every term is dropped
-    for (int j = j0 + (tid >> 1); j < js0; j += NT / 2) {
+    for (int j = j0 + (tid >> 1); j < js0; j += 32 * W) {
 #pragma unroll
         for (int f = 0; f < FW; f++)
             if (f < nf) a.out[qoff[f] + 2 * (base + j) + (tid & 1)] = 0.0;
@@ -677,32 +677,20 @@ __device__ __forceinline__ void analys_unit(
     // (indices clamped to valid entries, inactive lanes masked afterwards),
     // so the setup costs one memory round trip.
     AState<LP, FW> s;
-    int sj[LP];
     const bool from_rst = rst >= 0 && js0 == j0;
-    // no lane starts inside the unit (window -1): its start states are not
-    // needed, all lanes come live from the restart state
-    const bool starts = jwin >= js0;
     {
         const bool odd = lane & 1;
-        int pc[LP], jv[LP];
+        int pc[LP];
         bool act[LP];
         double xv[LP], wl[LP];
-        double2 y[LP], r[LP], fn[LP][FW], fsth[LP][FW];
+        double2 r[LP], fn[LP][FW], fsth[LP][FW];
 #pragma unroll
         for (int p = 0; p < LP; p++) {
             const int pair = pb + p * 64 + lane;
             act[p] = pair < npair;
             pc[p] = act[p] ? pair : 0;
-            const size_t q = (size_t)m * npair + pc[p];
             xv[p] = P->xp[pc[p]];
             wl[p] = P->wq[pc[p]];
-            if (starts) {
-                y[p] = *(const double2*)(P->inj_y + 2 * q);
-                jv[p] = P->inj_j[q];
-            } else {
-                y[p] = make_double2(0.0, 0.0);
-                jv[p] = nj;
-            }
 #pragma unroll
             for (int f = 0; f < FW; f++) {
                 const double* F = a.in + foff[f];
@@ -720,9 +708,6 @@ __device__ __forceinline__ void analys_unit(
         }
 #pragma unroll
         for (int p = 0; p < LP; p++) {
-            // lane starts: steps in registers, stored states in LDS
-            start_y[wv][p][lane] = y[p];
-            sj[p] = act[p] ? jv[p] : nj;
             s.x[p] = act[p] ? xv[p] : 0.0;
             s.ua[p] = act[p] ? r[p].x : 0.0;
             s.ub[p] = act[p] ? r[p].y : 0.0;
@@ -744,7 +729,7 @@ __device__ __forceinline__ void analys_unit(
     }
 
     // Warm L2 with the beta entries of this unit (one word per 64-byte line
-    // per lane, consumed at the end; see the synthesis kernel).
+    // per lane, consumed at the end).
     __builtin_amdgcn_sched_barrier(0);
     unsigned pf_sink;
     {
@@ -752,13 +737,13 @@ __device__ __forceinline__ void analys_unit(
         const int off = lane * 64;
         pf_sink = *(const unsigned*)((const char*)(P->beta + base + js0) + (off < nbytes ? off : 0));
     }
+    __builtin_amdgcn_s_setprio(0);
     const double cm = (m == 0 || !a.adjoint) ? 1.0 : 2.0;
-    const int o = tid / PR;        // output of this thread: (row, component)
-    const int h = tid % PR;        // its part of the columns
+    const int o = lane / PR;       // output of this lane: (row, component)
+    const int h = lane % PR;       // its part of the columns
     const int row = o >> 1, comp = o & 1;
     const int t_out = row / FW;
     const int f_out = row % FW;
-    const int col = wv * 64 + lane;  // this thread's column
     cdp gam_tab = (cdp)P->gamma + base;
 
     // beta is loaded one half ahead (the second half's while the first
@@ -793,12 +778,8 @@ __device__ __forceinline__ void analys_unit(
         double part[NK];
 #pragma unroll
         for (int k = 0; k < NK; k++) part[k] = red[row][2 * (k * PR + h) + comp];
-        // gamma of this thread's output in that pass, needed after the steps
-        const double gl = gam_tab[min(max(c - SC, js0) + t_out, j1 - 1)];
-        // several waves: every wave has read the previous pass's rows before
-        // any wave writes this pass's (before the next scalar loads are
-        // issued, so that the barrier's wait does not drain them)
-        if (W > 1 && compute) __syncthreads();
+        // gamma of this lane's output in that pass, needed after the steps
+        const double gl = W > 1 ? 0.0 : gam_tab[min(max(c - SC, js0) + t_out, j1 - 1)];
         if (compute) {
             const int cn = c + SC;
             // two halves: the second half's beta; one half: the next pass's
@@ -807,8 +788,8 @@ __device__ __forceinline__ void analys_unit(
             shn = (cn < j1 && cn % kSegLen == 0) ? segexp[cn / kSegLen] : 0;
             __builtin_amdgcn_sched_barrier(0);
             if (sh != 0) rescale(s.ua, s.ub, sh);
-            if (mk[0] != 0u && c <= jwin) start_slots(s.ua, s.ub, sj, start_y[wv], mk[0], c);
-            analys_half_from<LP, FW, RS>(lv[0] ? __builtin_ctz(lv[0]) : LP, s, bh0.v, &red[0][col], 0);
+            if (mk[0] != 0u && c <= jwin) start_slots(s.ua, s.ub, P, m, pb, mk[0], c);
+            analys_half_from<LP, FW, RS>(lv[0] ? __builtin_ctz(lv[0]) : LP, s, bh0.v, &red[0][lane], 0);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (NH == 2) {
                 __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): bh1, the masks, the shift
@@ -816,8 +797,8 @@ __device__ __forceinline__ void analys_unit(
                 load_blk(bh0, bet + cn);
                 __builtin_amdgcn_sched_barrier(0);
                 const int c1 = c + kInject;
-                if (mk[1] != 0u && c1 <= jwin) start_slots(s.ua, s.ub, sj, start_y[wv], mk[1], c1);
-                analys_half_from<LP, FW, RS>(lv[1] ? __builtin_ctz(lv[1]) : LP, s, bh1.v, &red[0][col], kInject);
+                if (mk[1] != 0u && c1 <= jwin) start_slots(s.ua, s.ub, P, m, pb, mk[1], c1);
+                analys_half_from<LP, FW, RS>(lv[1] ? __builtin_ctz(lv[1]) : LP, s, bh1.v, &red[0][lane], kInject);
             } else {
                 bh0 = bh1;
             }
@@ -835,13 +816,34 @@ __device__ __forceinline__ void analys_unit(
 #pragma unroll
             for (int q = 1; q < PR; q <<= 1) sum += __shfl_xor(sum, q);
             const int j_out = c - SC + t_out;
-            if (h == 0 && j_out < j1 && f_out < nf) {
-                double val = cm * gl * sum;
-                if (m == 0 && comp == 1) val = 0.0;
-                a.out[qoff[f_out] + 2 * (base + j_out) + comp] = val;
+            if constexpr (W == 1) {
+                if (h == 0 && j_out < j1 && f_out < nf) {
+                    double val = cm * gl * sum;
+                    if (m == 0 && comp == 1) val = 0.0;
+                    a.out[qoff[f_out] + 2 * (base + j_out) + comp] = val;
+                }
+            } else {
+                const int jc = (c - SC - js0) & ~(kWideChunk - 1);  // first degree of the chunk, from js0
+                if (h == 0) acc[wid][((j_out - js0 - jc) * FW + f_out) * 2 + comp] = sum;
+                if (c >= j1 || (c - js0) % kWideChunk == 0) {
+                    // the chunk's last pass is in: add up the waves' sums
+                    __syncthreads();
+                    const int n = min(kWideChunk, j1 - js0 - jc) * FW * 2;
+                    for (int e = tid; e < n; e += 64 * W) {
+                        double v = acc[0][e];
+#pragma unroll
+                        for (int w = 1; w < W; w++) v += acc[w][e];
+                        const int f = (e >> 1) % FW, j = js0 + jc + (e >> 1) / FW;
+                        if (f < nf) {
+                            v *= cm * P->gamma[base + j];
+                            if (m == 0 && (e & 1)) v = 0.0;
+                            a.out[qoff[f] + 2 * (base + j) + (e & 1)] = v;
+                        }
+                    }
+                    __syncthreads();
+                }
             }
         }
-        if (W > 1) __syncthreads();
     }
     // keeps the prefetch load alive; nfields is never negative
     if (a.nfields < 0) a.out[lane] = (double)pf_sink;
@@ -852,9 +854,9 @@ template <int LP, int FW, int W>
 __global__ void __launch_bounds__(64 * W) k_legendre_analys(LegArgs a)
 {
     using G = AnalysGeom<LP, FW, W>;
-    __shared__ double red[G::NR][G::RS];
-    __shared__ double2 start_y[W][LP][64];  // stored lane start states
-    analys_unit<LP, FW, W>(a, blockIdx.x, red, start_y);
+    __shared__ double red[W][G::NR][G::RS];
+    __shared__ double acc[W][G::NA];
+    analys_unit<LP, FW, W>(a, blockIdx.x, red, acc);
 }
 
 // ---------------------------------------------------------------------------
