@@ -30,9 +30,11 @@ FLAGS = [
 # loop-carried; in the default (accumulator-register) form the compiler
 # copies every accumulator between register files at each step and needs
 # 296-320 registers per lane for the widest tilings (one wave per SIMD).  The
-# VGPR form needs no copies and 226-252 registers (two waves per SIMD).
+# VGPR form needs no copies and 226-252 registers (two waves per SIMD).  The
+# several-field analysis holds its B operands for the whole unit likewise.
 FILE_FLAGS = {
     "ptable.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "analys_mf.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 
 

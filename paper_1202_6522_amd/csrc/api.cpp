@@ -224,7 +224,18 @@ int f_to_leg(const Plan& p, const double* F, double* Q, int nfields, int adjoint
     l.adjoint = adjoint;
     {
         ProfScope ps(PK_LEG_ANALYS, stream);
-        e = launch_legendre_analys(l, stream);
+        if (const int mf = p.tiling.auto_fw ? mf_fields(p.npair, p.nlm, nfields) : 0) {
+            // the longest pieces that still give two waves for each of the
+            // 2048 slots: a unit's set-up costs as much as some 40 degrees
+            const long groups = (nfields + mf - 1) / mf;
+            int k = kMfLists - 1;
+            while (k > 0 && (long)(p.mf_units[k].size() / kUnitInts) * groups * mf_waves(p.npair, mf) < 4096) k--;
+            if (k > 0) l.units = dev_table_int(p, TB_MF_UNITS + k - 1);
+            l.nunits = (int)(p.mf_units[k].size() / kUnitInts);
+            e = launch_legendre_analys_mf(l, p.npair, mf, stream);
+        } else {
+            e = launch_legendre_analys(l, stream);
+        }
     }
     if (e) return hip_fail(e, "legendre analysis launch");
     return SHTN_OK;

@@ -513,7 +513,15 @@ int rebuild_units(Plan& p, std::string& err)
     if (S % kSegLen) { err = "split must be a multiple of 32"; return -1; }
     p.split_used = S;
     struct AU { int m, j0, j1, js, jw, rst; long cost; };
-    std::vector<std::vector<int>> rj(M + 1);  // restart steps of each order, ascending
+    // restart slots: order by order, each order's restart steps S, 2 S, ...
+    std::vector<std::vector<int>> rj(M + 1);
+    std::vector<int> rbase(M + 1, 0);
+    int nrst = 0;
+    for (int m = 0; m <= M; m++) {
+        rbase[m] = nrst;
+        for (int j0 = S; j0 < L - m + 1; j0 += S) rj[m].push_back(j0);
+        nrst += (int)rj[m].size();
+    }
     auto make_piece = [&](int m, int j0, int j1) {
         int jmin, jmax;
         // lanes started before j0 are live from the restart state; the piece
@@ -531,27 +539,23 @@ int rebuild_units(Plan& p, std::string& err)
             js = j1;  // nothing starts: the piece only writes zeros
             jw = -1;
         }
-        int r = -1;
-        if (j0 > 0) {
-            r = (int)rj[m].size();
-            rj[m].push_back(j0);
-        }
-        return AU{m, j0, j1, js, jw, r, js < j1 ? analys_unit_cost(p, m, js, j1) : 0};
+        return AU{m, j0, j1, js, jw, j0 > 0 ? rbase[m] + j0 / S - 1 : -1, js < j1 ? analys_unit_cost(p, m, js, j1) : 0};
     };
-    std::vector<std::vector<AU>> pieces(M + 1);
-    std::vector<long> mcost(M + 1, 0);
-    for (int m = 0; m <= M; m++) {
-        const int nj = L - m + 1;
-        for (int j0 = 0; j0 < nj; j0 += S) {
-            pieces[m].push_back(make_piece(m, j0, std::min(j0 + S, nj)));
-            mcost[m] += pieces[m].back().cost;
+    // the unit list for pieces of `len` degrees (a multiple of S)
+    auto analys_list = [&](int len, std::vector<int>& units) {
+        std::vector<std::vector<AU>> pieces(M + 1);
+        std::vector<long> mcost(M + 1, 0);
+        for (int m = 0; m <= M; m++) {
+            const int nj = L - m + 1;
+            for (int j0 = 0; j0 < nj; j0 += len) {
+                pieces[m].push_back(make_piece(m, j0, std::min(j0 + len, nj)));
+                mcost[m] += pieces[m].back().cost;
+            }
         }
-    }
-    std::vector<int> ms(M + 1);
-    for (int m = 0; m <= M; m++) ms[m] = m;
-    std::stable_sort(ms.begin(), ms.end(), [&](int a, int b) { return mcost[a] > mcost[b]; });
-    std::vector<std::vector<AU>> xq(kXcds);
-    {
+        std::vector<int> ms(M + 1);
+        for (int m = 0; m <= M; m++) ms[m] = m;
+        std::stable_sort(ms.begin(), ms.end(), [&](int a, int b) { return mcost[a] > mcost[b]; });
+        std::vector<std::vector<AU>> xq(kXcds);
         long xload[kXcds] = {0};
         for (int m : ms) {
             int x = 0;
@@ -560,31 +564,26 @@ int rebuild_units(Plan& p, std::string& err)
             xload[x] += mcost[m];
             xq[x].insert(xq[x].end(), pieces[m].begin(), pieces[m].end());
         }
-    }
-    for (auto& q : xq)
-        std::stable_sort(q.begin(), q.end(), [](const AU& a, const AU& b) { return a.cost > b.cost; });
-    // restart slots: order by order, each order's restart steps ascending
-    int nrst = 0;
-    std::vector<int> rbase(M + 1, 0);
-    for (int m = 0; m <= M; m++) {
-        rbase[m] = nrst;
-        nrst += (int)rj[m].size();
-    }
-    p.analys_units.clear();
-    size_t qlen = 0;
-    for (auto& q : xq) qlen = std::max(qlen, q.size());
-    for (size_t k = 0; k < qlen; k++) {
-        for (int x = 0; x < kXcds; x++) {
-            int u[kUnitInts] = {0, nf, 0, -1, 0, 0, 0, 0, -1, 0, 0, 0};
-            if (k < xq[x].size()) {
-                const AU& a = xq[x][k];
-                const int v[kUnitInts] = {0, nf, 0, a.m, a.js, a.jw, a.j0, a.j1,
-                                          a.rst >= 0 ? rbase[a.m] + a.rst : -1, 0, 0, 0};
-                std::copy(v, v + kUnitInts, u);
+        for (auto& q : xq)
+            std::stable_sort(q.begin(), q.end(), [](const AU& a, const AU& b) { return a.cost > b.cost; });
+        units.clear();
+        size_t qlen = 0;
+        for (auto& q : xq) qlen = std::max(qlen, q.size());
+        for (size_t k = 0; k < qlen; k++) {
+            for (int x = 0; x < kXcds; x++) {
+                int u[kUnitInts] = {0, nf, 0, -1, 0, 0, 0, 0, -1, 0, 0, 0};
+                if (k < xq[x].size()) {
+                    const AU& a = xq[x][k];
+                    const int v[kUnitInts] = {0, nf, 0, a.m, a.js, a.jw, a.j0, a.j1, a.rst, 0, 0, 0};
+                    std::copy(v, v + kUnitInts, u);
+                }
+                units.insert(units.end(), u, u + kUnitInts);
             }
-            p.analys_units.insert(p.analys_units.end(), u, u + kUnitInts);
         }
-    }
+    };
+    analys_list(S, p.analys_units);
+    // longer pieces for calls of many fields (analys_mf.hip)
+    for (int k = 0; k < kMfLists; k++) analys_list(S << k, p.mf_units[k]);
     p.rst_y.assign((size_t)nrst * np * 2, 0.0);
     // restart states, orders split over host threads
     unsigned nth = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
@@ -663,6 +662,7 @@ void build_image(Plan& p)
     place(TB_SYNTH_UNITS, p.synth_units);
     place(TB_ANALYS_UNITS, p.analys_units);
     place(TB_CK_MASK, p.ck_mask);
+    for (int k = 1; k < kMfLists; k++) place(TB_MF_UNITS + k - 1, p.mf_units[k]);
     p.image.resize(off, 0);
 }
 

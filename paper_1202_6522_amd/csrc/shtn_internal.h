@@ -99,8 +99,13 @@ enum DevTable {
     TB_SYNTH_UNITS,
     TB_ANALYS_UNITS,
     TB_CK_MASK,
-    TB_COUNT
+    TB_MF_UNITS,  // kMfLists - 1 tables (list 0 is TB_ANALYS_UNITS)
+    TB_COUNT = TB_MF_UNITS + 2
 };
+// Unit lists of the several-field analysis: pieces of 1, 2 and 4 times the
+// plan's split.
+constexpr int kMfLists = 3;
+static_assert(TB_COUNT == TB_MF_UNITS + kMfLists - 1, "one table per further list");
 
 // Lane-start summaries per block of 64 latitude pairs (the pair slot of a
 // wave lane: pairs [64 b, 64 b + 64) form block b).  blk_first[m][b]: the
@@ -183,6 +188,7 @@ struct Plan {
     std::vector<double> rst_y;
     std::vector<double> tw, rtw;
     std::vector<int> synth_units, analys_units;
+    std::vector<int> mf_units[kMfLists];
     std::vector<int> first_pair;              // per m: first latitude pair kept by the polar cut
     double min_own_state = 0.0;               // see min_start_state
     std::vector<int> blk_first;               // (M+1) x nblk, see TB_BLK_FIRST
@@ -349,6 +355,28 @@ int launch_vec_spec_out(const DevPlan* plan, int L, int M, const double* A4, dou
                         int nn, void* stream);
 int launch_legendre_synth(const LegLaunch& a, void* stream);
 int launch_legendre_analys(const LegLaunch& a, void* stream);
+// Several fields of one plan with the sums on the matrix cores (analys_mf.hip).
+// Fields per unit: 8, 4, or 0 where the vector kernel is the better one.  A
+// unit of eight fields costs about as much as 6.1 fields in the vector kernel,
+// one of four 3.45, whether or not all are there (lmax 1023: 8 fields 267 us
+// against 348, 4 fields 152 against 178, 3 fields 148 against 136), and small
+// calls are bound by latency (lmax 255: 8 fields 18.8 against 17.7, 16 fields
+// 22.6 against 27.7; lmax 383, 8 fields 41 both).
+inline int mf_fields(int npair, long nlm, int nfields)
+{
+    if ((double)nlm * npair * nfields < 6e7) return 0;
+    const double vec = nfields, four = (nfields + 3) / 4 * 3.45,
+                 eight = npair <= 1024 ? (nfields + 7) / 8 * 6.1 : vec + four;
+    return vec <= four && vec <= eight ? 0 : (eight <= four ? 8 : 4);
+}
+// Waves of a unit (each covers 256 latitude pairs with four fields, 128 with eight).
+inline int mf_waves(int npair, int fields)
+{
+    int w = 1;
+    while (1024 / fields * w < npair) w *= 2;
+    return w;
+}
+int launch_legendre_analys_mf(const LegLaunch& a, int npair, int fields, void* stream);
 
 struct FftLaunch {
     const DevPlan* plans;     // device plan array
