@@ -56,9 +56,8 @@ void plan_ranges(const Plan& p, std::vector<Range>& r)
 
 int rows_per_block(const Plan& p)
 {
-    // rows of K points that fill one FFT workgroup (4096 points)
-    const int cap = fft_rows_cap(p.K);
-    int r = p.tiling.fft_rows > 0 ? p.tiling.fft_rows : cap;
+    const int cap = fft_rows_cap(p.K);  // rows of K points that fill the largest workgroup
+    int r = p.tiling.fft_rows > 0 ? p.tiling.fft_rows : fft_rows_auto(p.K);
     if (r > cap) r = cap;
     if (r > p.nlat) r = p.nlat;
     return r;

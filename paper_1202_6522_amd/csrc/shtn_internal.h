@@ -397,6 +397,7 @@ struct FftLaunch {
 };
 int launch_c2r(const FftLaunch& a, void* stream);
 int fft_rows_cap(int K);     // rows of K complex points held by one FFT workgroup
+int fft_rows_auto(int K);    // rows per workgroup unless the caller sets them
 int launch_r2c(const FftLaunch& a, void* stream);
 
 }  // namespace shtn
