@@ -10,6 +10,7 @@ raises if libshtn.so has not been built (there is no CPU fallback).
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 import re
 
@@ -415,6 +416,10 @@ def shtn_last_error_detail():
 # --- torch plumbing --------------------------------------------------------
 
 def _stream_ptr(torch, device):
+    # the raw handle, without the Stream object around it: 3.4 us of a call's
+    # 16 on the host at lmax 31 (with math.prod for np.prod: calls of 12 us)
+    if device.type == "cuda" and device.index is not None:
+        return torch._C._cuda_getCurrentRawStream(device.index)
     return torch.cuda.current_stream(device).cuda_stream
 
 
@@ -576,7 +581,7 @@ class Plan:
         import torch
         Q = self._spec_in(Q)
         lead = Q.shape[:-1]
-        nf = int(np.prod(lead)) if len(lead) else 1
+        nf = math.prod(lead)
         out = torch.empty(lead + (self.nlat, self.nphi), dtype=torch.float64, device=Q.device)
         fn(self.handle, Q.data_ptr(), out.data_ptr(), nf, self.workspace(nf),
            _stream_ptr(torch, Q.device))
@@ -586,7 +591,7 @@ class Plan:
         import torch
         g = self._grid_in(g)
         lead = g.shape[:-2]
-        nf = int(np.prod(lead)) if len(lead) else 1
+        nf = math.prod(lead)
         out = torch.empty(lead + (self.nlm,), dtype=torch.complex128, device=g.device)
         fn(self.handle, g.data_ptr(), out.data_ptr(), nf, self.workspace(nf),
            _stream_ptr(torch, g.device))
@@ -625,7 +630,7 @@ class Plan:
         if S.shape != T.shape:
             raise ValueError("S and T must have the same shape")
         lead = S.shape[:-1]
-        nf = int(np.prod(lead)) if len(lead) else 1
+        nf = math.prod(lead)
         vt = torch.empty(lead + (self.nlat, self.nphi), dtype=torch.float64, device=S.device)
         vp = torch.empty_like(vt)
         fn(self.handle, S.data_ptr(), T.data_ptr(), vt.data_ptr(), vp.data_ptr(), nf,
@@ -639,7 +644,7 @@ class Plan:
         if vt.shape != vp.shape:
             raise ValueError("V_theta and V_phi must have the same shape")
         lead = vt.shape[:-2]
-        nf = int(np.prod(lead)) if len(lead) else 1
+        nf = math.prod(lead)
         S = torch.empty(lead + (self.nlm,), dtype=torch.complex128, device=vt.device)
         T = torch.empty_like(S)
         fn(self.handle, vt.data_ptr(), vp.data_ptr(), S.data_ptr(), T.data_ptr(), nf,
