@@ -26,7 +26,7 @@
 // (library events, us, vector kernel and this one): lmax 511, 16 fields, 123
 // and 84; lmax 1023, 4 fields, 178 and 152, 8 fields, 348 and 267; lmax 2047, 4
 // fields, 1295 and 987.  Tried and not kept: v_mfma_f64_16x16x4 for eight fields
-// in passes of 32 degrees (lmax 511, 16 fields: 108), two fields (slower than
+// in passes of 32 degrees (lmax 511, 16 fields: 108), two scalar fields (slower than
 // the vector kernel at lmax 511 and 1023).
 #include <algorithm>
 
@@ -43,7 +43,8 @@ static_assert(kOct == kInject, "one start checkpoint per pass");
 // One pass over the slots PF .. LP-1 (the slots below belong to latitude
 // blocks that have not started): d[q][c] += the octet's products of parity q
 // with column group c (fields 2 c and 2 c + 1).
-template <int LP, int CG, int PF>
+// XT: with x P in place of P, whose parity is the other one.
+template <int LP, int CG, int PF, bool XT = false>
 __device__ __forceinline__ void mf_octet(const double (&x)[LP], double (&ua)[LP], double (&ub)[LP],
                                          const double (&b)[kOct], const double (&g)[LP][4][2][CG],
                                          double (*rows)[kMfStride], double (&d)[2][CG])
@@ -65,7 +66,7 @@ __device__ __forceinline__ void mf_octet(const double (&x)[LP], double (&ua)[LP]
                 v[t + 1] = ub[p];
             }
 #pragma unroll
-            for (int t = 0; t < kOct; t++) rows[(t & 1) * 4 + (t >> 1)][lane] = v[t];
+            for (int t = 0; t < kOct; t++) rows[(t & 1) * 4 + (t >> 1)][lane] = XT ? x[p] * v[t] : v[t];
 #pragma unroll
             for (int q = 0; q < 2; q++)
 #pragma unroll
@@ -79,18 +80,22 @@ __device__ __forceinline__ void mf_octet(const double (&x)[LP], double (&ua)[LP]
                 for (int q = 0; q < 2; q++)
 #pragma unroll
                     for (int c = 0; c < CG; c++)
-                        d[q][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[o & 1][q][s], g[o][s][q][c], d[q][c], 0, 0, 0);
+                        d[q][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[o & 1][q][s], g[o][s][XT ? 1 - q : q][c], d[q][c], 0, 0, 0);
         }
     }
 }
 
 // One workgroup per unit (degrees [j0, j1) of one order), 2 CG fields; W waves
-// cover 64 LP latitude pairs each.  CG = 2 or 4 column groups: four or eight fields.
-template <int LP, int CG, int W>
+// cover 64 LP latitude pairs each.  CG = 2 or 4 column groups: four or eight
+// fields; with CG = 1 the four columns are the parts of two.  VEC: the fields
+// are the components of tangent vectors (vector.hip): inputs are divided by
+// sin(theta), and the unit with the order's last degree, L, also gives the sum
+// with x P_L in place of P_L (a.top).
+template <int LP, int CG, int W, bool VEC>
 __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
 {
     constexpr int NF = 2 * CG;
-    constexpr int NV = CG / 2;          // outputs of an octet per lane
+    constexpr int NV = CG > 1 ? CG / 2 : 1;  // outputs of an octet per lane
     constexpr int kMfChunk = 128 / NV;  // degrees whose sums several waves exchange at once
     __shared__ double rows_w[W][kOct][kMfStride];
     // sums of a chunk per wave: one octet is NV values per lane
@@ -127,25 +132,31 @@ __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
     // degrees before the first started lane: every term is dropped
     for (int e = tid; e < (js0 - j0) * 2; e += 64 * W)
         for (int f = 0; f < nf; f++) a.out[(long)(field0 + f) * 2 * nlm + 2 * (base + j0) + e] = 0.0;
-    if (js0 >= j1) return;
+    const bool last = VEC && j1 == L - m + 1;
+    if (js0 >= j1) {
+        if (last && tid < 2 * nf) a.top[2 * ((long)(field0 + (tid >> 1)) * (P->M + 1) + m) + (tid & 1)] = 0.0;
+        return;
+    }
 
     // Columns: group 0 holds the real parts of fields 0 to 3, 1 their
     // imaginary parts (2 and 3 those of fields 4 to 7), so lane n of a quad
     // loads whole complex values of field n (and n + 4).  (Fields past the
-    // last repeat it and are not stored.)
+    // last repeat it and are not stored.)  A single group holds field n / 2,
+    // real part at even n, imaginary part at odd n.
     double x[LP], ua[LP], ub[LP];
     double g[LP][4][2][CG];
     const bool from_rst = rst >= 0 && js0 == j0;
     // every load of the set-up is issued before any is used
     {
-        double w[LP][4];
+        double w[LP][4], xs[LP][4];
         double2 r[LP];
         // byte offsets from the first field (at most eight fields of 268 MB)
         gcp F = (gcp)(a.in + (long)field0 * 2 * P->f_size + 2 * m * kFTile);
         unsigned fo[NV];
 #pragma unroll
         for (int v = 0; v < NV; v++)
-            fo[v] = (unsigned)min(4 * v + (lane & 3), nf - 1) * (unsigned)(P->f_size * 16);
+            fo[v] = CG > 1 ? (unsigned)min(4 * v + (lane & 3), nf - 1) * (unsigned)(P->f_size * 16)
+                           : (unsigned)min((lane >> 1) & 1, nf - 1) * (unsigned)(P->f_size * 16) + 8 * (lane & 1);
         const unsigned ts16 = (unsigned)fts * 16;
         gcp xp = (gcp)P->xp, wq = (gcp)P->wq;
         auto lat_off = [&](int i) { return (unsigned)(i >> kFTileLg) * ts16 + (unsigned)(i & (kFTile - 1)) * 16; };
@@ -157,14 +168,20 @@ __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
                 // B rows: the pairs whose values sit in lanes 16 k + 4 b + s
                 const int pair = min(pb + p * 64 + (lane & 60) + s, npair - 1);
                 w[p][s] = ld1(wq, 8 * (unsigned)pair);
+                if constexpr (VEC) xs[p][s] = ld1(xp, 8 * (unsigned)pair);
                 const unsigned on = lat_off(pair), os = lat_off(nlat - 1 - pair);
 #pragma unroll
                 for (int v = 0; v < NV; v++) {
-                    const double2 vn = ld2(F, fo[v] + on), vs = ld2(F, fo[v] + os);
-                    g[p][s][0][2 * v] = vn.x;
-                    g[p][s][0][2 * v + 1] = vn.y;
-                    g[p][s][1][2 * v] = vs.x;
-                    g[p][s][1][2 * v + 1] = vs.y;
+                    if constexpr (CG > 1) {
+                        const double2 vn = ld2(F, fo[v] + on), vs = ld2(F, fo[v] + os);
+                        g[p][s][0][2 * v] = vn.x;
+                        g[p][s][0][2 * v + 1] = vn.y;
+                        g[p][s][1][2 * v] = vs.x;
+                        g[p][s][1][2 * v + 1] = vs.y;
+                    } else {
+                        g[p][s][0][0] = ld1(F, fo[v] + on);
+                        g[p][s][1][0] = ld1(F, fo[v] + os);
+                    }
                 }
             }
         }
@@ -186,7 +203,8 @@ __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
             for (int s = 0; s < 4; s++) {
                 const int pair = pb + p * 64 + (lane & 60) + s;
                 const bool middle = (nlat & 1) && pair == npair - 1;
-                const double wt = pair >= npair ? 0.0 : (a.adjoint ? (middle ? 0.5 : 1.0) : w[p][s]);
+                double wt = pair >= npair ? 0.0 : (a.adjoint ? (middle ? 0.5 : 1.0) : w[p][s]);
+                if constexpr (VEC) wt = wt / sqrt((1.0 - xs[p][s]) * (1.0 + xs[p][s]));
 #pragma unroll
                 for (int c = 0; c < CG; c++) {
                     const double vn = g[p][s][0][c], vs = g[p][s][1][c];
@@ -202,8 +220,9 @@ __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
     // picks parity q = b % 2 and column group b / 2 (+ 2 v) of row i = lane / 16
     const int oq = (lane >> 2) & 1, oc = (lane >> 3) & 1;
     const int oj = 2 * (lane >> 4) + oq;
-    const int of = lane & 3;  // + 4 v
-    const int comp = oc;
+    const int of = CG > 1 ? lane & 3 : (lane >> 1) & 1;  // + 4 v
+    const int comp = CG > 1 ? oc : lane & 1;
+    const bool mine = CG > 1 || oc == 0;  // (a single group: lane groups 2 and 3 repeat 0 and 1)
     double* out = a.out + (long)(field0 + of) * 2 * nlm + 2 * base + comp;
     gcp gam = (gcp)(P->gamma + base);
     const double cm = (m == 0 || !a.adjoint) ? 1.0 : 2.0;
@@ -233,10 +252,23 @@ __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
         if (sh != 0) rescale(ua, ub, sh);
         if (mk != 0u && c <= jwin) start_slots(ua, ub, P, m, pb, mk, c);
         double d[2][CG];
+        auto clear = [&] {
 #pragma unroll
-        for (int q = 0; q < 2; q++)
+            for (int q = 0; q < 2; q++)
 #pragma unroll
-            for (int k = 0; k < CG; k++) d[q][k] = 0.0;
+                for (int k = 0; k < CG; k++) d[q][k] = 0.0;
+        };
+        clear();
+        // the states before the order's last degrees, which then run again with x P
+        double va[LP], vb[LP];
+        const bool again = last && cn >= j1;
+        if (VEC && again) {
+#pragma unroll
+            for (int p = 0; p < LP; p++) {
+                va[p] = ua[p];
+                vb[p] = ub[p];
+            }
+        }
         switch (lv ? __builtin_ctz(lv) : LP) {
         case 0: mf_octet<LP, CG, 0>(x, ua, ub, b, g, rows, d); break;
         case 1: mf_octet<LP, CG, (1 < LP ? 1 : LP)>(x, ua, ub, b, g, rows, d); break;
@@ -248,17 +280,20 @@ __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
         // adds up parity b % 2 of column group b / 2
         double val[NV];
         double* sums = &rows[0][0];
+        auto sum_b = [&] {
 #pragma unroll
-        for (int v = 0; v < NV; v++) {
+            for (int v = 0; v < NV; v++) {
 #pragma unroll
-            for (int k = 0; k < 2; k++)
+                for (int k = 0; k < (CG > 1 ? 2 : 1); k++)
 #pragma unroll
-                for (int q = 0; q < 2; q++) sums[(2 * k + q) * kSumStride + lane] = d[q][2 * v + k];
-            const double* br = sums + ((lane >> 2) & 3) * kSumStride + (lane & 51);
-            val[v] = (br[0] + br[4]) + (br[8] + br[12]);
-        }
+                    for (int q = 0; q < 2; q++) sums[(2 * k + q) * kSumStride + lane] = d[q][2 * v + k];
+                const double* br = sums + ((lane >> 2) & (CG > 1 ? 3 : 1)) * kSumStride + (lane & 51);
+                val[v] = (br[0] + br[4]) + (br[8] + br[12]);
+            }
+        };
+        sum_b();
         auto store = [&](double s, int j, double gm, int v) {
-            if (of + 4 * v < nf && j < j1)
+            if (mine && of + 4 * v < nf && j < j1)
                 out[(long)(4 * v) * 2 * nlm + 2 * j] = m == 0 && comp == 1 ? 0.0 : cm * gm * s;
         };
         if constexpr (W == 1) {
@@ -286,6 +321,38 @@ __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
                 __syncthreads();
             }
         }
+        if constexpr (VEC) {
+            if (again) {
+                clear();
+                switch (lv ? __builtin_ctz(lv) : LP) {
+                case 0: mf_octet<LP, CG, 0, true>(x, va, vb, b, g, rows, d); break;
+                case 1: mf_octet<LP, CG, (1 < LP ? 1 : LP), true>(x, va, vb, b, g, rows, d); break;
+                case 2: mf_octet<LP, CG, (2 < LP ? 2 : LP), true>(x, va, vb, b, g, rows, d); break;
+                case 3: mf_octet<LP, CG, (3 < LP ? 3 : LP), true>(x, va, vb, b, g, rows, d); break;
+                default: break;
+                }
+                sum_b();
+                if constexpr (W > 1) {
+                    // (the workgroup is past its last chunk's sums)
+#pragma unroll
+                    for (int v = 0; v < NV; v++) acc[wid][v * 64 + lane] = val[v];
+                    __syncthreads();
+#pragma unroll
+                    for (int v = 0; v < NV; v++) {
+                        val[v] = acc[0][v * 64 + lane];
+#pragma unroll
+                        for (int k = 1; k < W; k++) val[v] += acc[k][v * 64 + lane];
+                    }
+                }
+                if (wid == 0 && mine && c + oj == j1 - 1) {
+#pragma unroll
+                    for (int v = 0; v < NV; v++)
+                        if (of + 4 * v < nf)
+                            a.top[2 * ((long)(field0 + of + 4 * v) * (P->M + 1) + m) + comp] =
+                                m == 0 && comp == 1 ? 0.0 : cm * gl * val[v];
+                }
+            }
+        }
     }
 }
 
@@ -298,7 +365,7 @@ static int launch_mf_t(K kernel, int fields, const LegLaunch& l, void* stream)
     const int most = std::max(1, (1 << 25) / (l.nunits * W));
     for (int g0 = 0; g0 < groups; g0 += most) {
         const int ng = std::min(most, groups - g0);
-        LegArgs a{l.plans, l.units, l.q_off, l.f_off, l.in, l.out, l.nfields, l.adjoint, l.nunits, ng, g0, W};
+        LegArgs a{l.plans, l.units, l.q_off, l.f_off, l.in, l.out, l.nfields, l.adjoint, l.nunits, ng, g0, W, l.top};
         hipLaunchKernelGGL(kernel, dim3((unsigned)l.nunits * ng), dim3(64 * W), 0, (hipStream_t)stream, a);
     }
     return (int)hipGetLastError();
@@ -310,10 +377,18 @@ int launch_legendre_analys_mf(const LegLaunch& l, int npair, int nf, void* strea
     const int w = mf_waves(npair, nf);
     const int lp = npair <= 64 ? 1 : (npair <= 128 || nf == 8 ? 2 : 4);
 #define SHTN_M(LPV, CV, WV) \
-    if (nf == 2 * CV && lp == LPV && w == WV) return launch_mf_t<WV>(k_legendre_analys_mf<LPV, CV, WV>, 2 * CV, l, stream);
+    if (nf == 2 * CV && lp == LPV && w == WV)                                                        \
+        return l.top ? launch_mf_t<WV>(k_legendre_analys_mf<LPV, CV, WV, true>, 2 * CV, l, stream)   \
+                     : launch_mf_t<WV>(k_legendre_analys_mf<LPV, CV, WV, false>, 2 * CV, l, stream);
     SHTN_M(1, 2, 1) SHTN_M(2, 2, 1) SHTN_M(4, 2, 1) SHTN_M(4, 2, 2) SHTN_M(4, 2, 4) SHTN_M(4, 2, 8)
     SHTN_M(1, 4, 1) SHTN_M(2, 4, 1) SHTN_M(2, 4, 2) SHTN_M(2, 4, 4) SHTN_M(2, 4, 8)
 #undef SHTN_M
+    // one vector field
+#define SHTN_V(LPV, WV)                          \
+    if (nf == 2 && lp == LPV && w == WV && l.top) \
+        return launch_mf_t<WV>(k_legendre_analys_mf<LPV, 1, WV, true>, 2, l, stream);
+    SHTN_V(1, 1) SHTN_V(2, 1) SHTN_V(4, 1) SHTN_V(4, 2) SHTN_V(4, 4) SHTN_V(4, 8)
+#undef SHTN_V
     return (int)hipErrorInvalidValue;
 }
 

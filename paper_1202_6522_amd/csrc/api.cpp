@@ -111,7 +111,8 @@ int sp_args(const Plan& p, const double* in, double* out, int nfields, int adjoi
 
 // Legendre synthesis-type stage (synthesis or adjoint of the analysis):
 // spectra Q -> longitude coefficients F.
-int leg_to_f(const Plan& p, const double* Q, double* F, int nfields, int adjoint, void* stream)
+// top: null, or the vector transforms' terms with x P_L (vec_on_the_fly plans).
+int leg_to_f(const Plan& p, const double* Q, double* F, int nfields, int adjoint, void* stream, double* top = nullptr)
 {
     int e;
     if (stored_synth(p.algo)) {
@@ -129,13 +130,15 @@ int leg_to_f(const Plan& p, const double* Q, double* F, int nfields, int adjoint
     l.plans = dplan(p);
     l.units = dev_table_int(p, TB_SYNTH_UNITS);
     l.nunits = (int)(p.synth_units.size() / kUnitInts);
+    l.lp = p.tiling.synth_lp;
     l.fw = p.tiling.auto_fw ? synth_fw(nfields, l.nunits, p.tiling.synth_lp) : p.tiling.fw;
+    if (top) l.fw = std::min(l.fw, 4 / l.lp);
     l.grid_y = (nfields + l.fw - 1) / l.fw;
     l.in = Q;
     l.out = F;
     l.nfields = nfields;
     l.adjoint = adjoint;
-    l.lp = p.tiling.synth_lp;
+    l.top = top;
     {
         ProfScope ps(PK_LEG_SYNTH, stream);
         e = launch_legendre_synth(l, stream);
@@ -161,24 +164,30 @@ FftLaunch fft_launch(const Plan& p, const double* in, double* out, int nfields, 
     return f;
 }
 
-// Longitude synthesis: F -> grid (c2r).
-int f_to_grid(const Plan& p, const double* F, double* grid, int nfields, void* stream)
+// Longitude synthesis: F -> grid (c2r).  grid2: fields 2 f go to grid f of
+// `grid`, fields 2 f + 1 to grid f of `grid2`.
+int f_to_grid(const Plan& p, const double* F, double* grid, int nfields, void* stream, double* grid2 = nullptr)
 {
     int e;
     {
         ProfScope ps(PK_C2R, stream);
-        e = launch_c2r(fft_launch(p, F, grid, nfields, 1.0), stream);
+        FftLaunch l = fft_launch(p, F, grid, nfields, 1.0);
+        l.grid2 = grid2;
+        e = launch_c2r(l, stream);
     }
     return e ? hip_fail(e, "c2r launch") : SHTN_OK;
 }
 
 // Longitude analysis: grid -> F (r2c), F scaled by `scale`.
-int grid_to_f(const Plan& p, const double* grid, double* F, int nfields, double scale, void* stream)
+int grid_to_f(const Plan& p, const double* grid, double* F, int nfields, double scale, void* stream,
+              const double* grid2 = nullptr)
 {
     int e;
     {
         ProfScope ps(PK_R2C, stream);
-        e = launch_r2c(fft_launch(p, grid, F, nfields, scale), stream);
+        FftLaunch l = fft_launch(p, grid, F, nfields, scale);
+        l.grid2 = (double*)grid2;  // (read)
+        e = launch_r2c(l, stream);
     }
     return e ? hip_fail(e, "r2c launch") : SHTN_OK;
 }
@@ -194,7 +203,7 @@ int check_analys_stage(const Plan& p)
 }
 
 // Legendre analysis-type stage (analysis or adjoint of the synthesis): F -> Q.
-int f_to_leg(const Plan& p, const double* F, double* Q, int nfields, int adjoint, void* stream)
+int f_to_leg(const Plan& p, const double* F, double* Q, int nfields, int adjoint, void* stream, double* top = nullptr)
 {
     int e;
     if (stored_analys(p.algo)) {
@@ -223,7 +232,9 @@ int f_to_leg(const Plan& p, const double* F, double* Q, int nfields, int adjoint
     l.adjoint = adjoint;
     {
         ProfScope ps(PK_LEG_ANALYS, stream);
-        if (const int mf = p.tiling.auto_fw ? mf_fields(p.npair, p.nlm, nfields) : 0) {
+        l.top = top;
+        if (const int mf = top ? mf_vec_fields(p.npair, nfields)
+                               : (p.tiling.auto_fw ? mf_fields(p.npair, p.nlm, nfields) : 0)) {
             // the longest pieces that still give two waves for each of the
             // 2048 slots: a unit's set-up costs as much as some 40 degrees
             const long groups = (nfields + mf - 1) / mf;
@@ -606,6 +617,10 @@ size_t shtn_vec_work_bytes(shtn_plan_t plan, int nfields)
 }  // extern "C"
 
 namespace {
+// Two scalar passes per vector field, with the Legendre kernels' terms in x P_L,
+// instead of four: where the plan's kernels are the automatic on-the-fly ones.
+bool vec_on_the_fly(const Plan& p, bool stored) { return !stored && p.tiling.auto_fw; }
+
 // Vector synthesis-type sequence: spectra (S, T) -> grids (Vt, Vp).  adjoint:
 // the adjoint of the vector analysis ((S, T) / n(n+1), scalar stages in
 // their adjoint mode).
@@ -621,6 +636,15 @@ int vec_to_grid(shtn_plan_t plan, const double* S, const double* T, double* Vt, 
     double* Fv = (double*)(w + v.fv);
     double* Q4 = (double*)(w + v.q4);
     const long fs = f_layout(p.M, p.nlat).size;
+    if (vec_on_the_fly(p, stored_synth(p.algo))) {
+        // two spectra per field, then M + 1 terms with x P_L for each (in the
+        // place of four spectra: nlm > M)
+        double* top = Q4 + 4 * (size_t)nfields * p.nlm;
+        const int e = launch_vec_spread(dplan(p), p.L, p.M, S, T, Q4, top, nfields, adjoint, stream);
+        if (e) return hip_fail(e, "vector spectra launch");
+        if ((rc = leg_to_f(p, Q4, F4, 2 * nfields, adjoint, stream, top))) return rc;
+        return f_to_grid(p, F4, Vt, 2 * nfields, stream, Vp);
+    }
     int e = launch_vec_spec_in(dplan(p), p.L, p.M, S, T, Q4, nfields, adjoint, stream);
     if (e) return hip_fail(e, "vector spectra launch");
     if ((rc = leg_to_f(p, Q4, F4, 4 * nfields, adjoint, stream))) return rc;
@@ -646,6 +670,13 @@ int vec_to_spec(shtn_plan_t plan, const double* Vt, const double* Vp, double* S,
     double* Q4 = (double*)(w + v.q4);
     const long fs = f_layout(p.M, p.nlat).size;
     const double sc = adjoint ? 1.0 : 2.0 * 3.14159265358979323846 / p.nphi;
+    if (vec_on_the_fly(p, stored_analys(p.algo))) {
+        double* top = Q4 + 4 * (size_t)nfields * p.nlm;
+        if ((rc = grid_to_f(p, Vt, F4, 2 * nfields, sc, stream, Vp))) return rc;
+        if ((rc = f_to_leg(p, F4, Q4, 2 * nfields, adjoint, stream, top))) return rc;
+        const int e = launch_vec_gather(dplan(p), p.L, p.M, Q4, top, S, T, nfields, !adjoint, stream);
+        return e ? hip_fail(e, "vector spectra launch") : SHTN_OK;
+    }
     if ((rc = grid_to_f(p, Vt, Fv, nfields, sc, stream))) return rc;
     if ((rc = grid_to_f(p, Vp, Fv + 2 * (size_t)nfields * fs, nfields, sc, stream))) return rc;
     int e = launch_vec_f_in(dplan(p), fs, Fv, F4, nfields, stream);

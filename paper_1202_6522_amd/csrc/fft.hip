@@ -86,10 +86,18 @@ struct FftArgs {
     const long* f_off;     // per field F offset in doubles, or null (f * 2 f_size)
     const double* in;
     double* out;
+    double* grid2;         // second grid buffer of vector transforms, or null (see FftLaunch)
     int nfields;
     int rows_per_block;
     double scale;
 };
+
+// Offset of a field's grid (doubles) from the buffer that holds it.
+__device__ __forceinline__ size_t grid_off(const FftArgs& a, int f, int nlat, int nphi)
+{
+    return a.g_off ? (size_t)a.g_off[f] : (size_t)(a.grid2 ? f >> 1 : f) * nlat * nphi;
+}
+__device__ __forceinline__ bool in_grid2(const FftArgs& a, int f) { return a.grid2 && (f & 1); }
 
 // The fused operations are spelt out, here and in z_point: left to the
 // compiler, kernels built for different row lengths, or the two ways into the
@@ -575,7 +583,7 @@ __device__ __forceinline__ void c2r_rows(const FftArgs& a, const DevPlan& D, con
     const gdp tw = (gdp)D.tw;
     const gdp rtw = (gdp)D.rtw;
     const double* F = a.in + (a.f_off ? a.f_off[rb.field] : (long)rb.field * 2 * D.f_size);
-    double* g = a.out + (a.g_off ? a.g_off[rb.field] : (long)rb.field * nlat * nphi);
+    double* g = (in_grid2(a, rb.field) ? a.grid2 : a.out) + grid_off(a, rb.field, nlat, nphi);
     const int npts = rb.nrows << lgK;
     // the block's threads: whole waves, P points each; the others end here
     const int nt = (((npts + P - 1) / P) + 63) & ~63;
@@ -720,7 +728,7 @@ __device__ __forceinline__ void r2c_rows(const FftArgs& a, const DevPlan& D, con
     const int lgK = LGK > 0 ? LGK : __builtin_ctz(K), rs = row_shift(lgK);
     const gdp tw = (gdp)D.tw;
     const gdp rtw = (gdp)D.rtw;
-    const double* g = a.in + (a.g_off ? a.g_off[rb.field] : (long)rb.field * nlat * nphi);
+    const double* g = (in_grid2(a, rb.field) ? a.grid2 : a.in) + grid_off(a, rb.field, nlat, nphi);
     double* F = a.out + (a.f_off ? a.f_off[rb.field] : (long)rb.field * 2 * D.f_size);
     const int npts = rb.nrows << lgK;
     // the block's threads: whole waves, P points each; the others end here
@@ -868,7 +876,7 @@ __global__ void __launch_bounds__(fft_max_threads(P, LGK), fft_min_waves(P, LGK)
 
 static FftArgs fft_args(const FftLaunch& l)
 {
-    FftArgs a{l.plans, l.rowblocks, l.g_off, l.f_off, l.in, l.out, l.nfields, l.rows_per_block,
+    FftArgs a{l.plans, l.rowblocks, l.g_off, l.f_off, l.in, l.out, l.grid2, l.nfields, l.rows_per_block,
               l.scale};
     return a;
 }

@@ -121,6 +121,20 @@ __device__ __forceinline__ void synth_steps(SynthState<LP, FW>& s, const double 
     }
 }
 
+// Steps T .. TE-1 of a group, n of them (wave-uniform): the state stays that
+// of the order's last degree.
+template <int LP, int FW, int T, int TE>
+__device__ __forceinline__ void synth_tail(SynthState<LP, FW>& s, const double (&b)[kGroup], const double2 (&q)[FW], int n)
+{
+    if constexpr (T < TE) {
+        if (n > 0) {
+            keep_branch();
+            synth_step<LP, FW, T>(s, b[T], q);
+            synth_tail<LP, FW, T + 1, TE>(s, b, q, n - 1);
+        }
+    }
+}
+
 // Unit and field group of a synthesis wave.  The unit list is eight queues,
 // one per XCD (entry 8 s + x is entry s of XCD x's queue), each longest first;
 // every unit runs once per field group, the groups of a unit one after
@@ -155,7 +169,10 @@ __device__ __forceinline__ bool synth_unit(const LegArgs& a, int wave, int& unit
 template <int LP, int FW>
 constexpr int synth_waves() { return LP * FW == 8 ? 4 : 1; }
 
-template <int LP, int FW>
+// VEC: the fields are the components of tangent vectors (vector.hip): the sums
+// get a term top x P_L(x), whose P_L is the state after the order's last
+// degree, and are divided by sin(theta).
+template <int LP, int FW, bool VEC>
 __global__ void __launch_bounds__(64 * kSynthWaves, (synth_waves<LP, FW>())) k_legendre_synth(LegArgs a)
 {
     // wave-uniform for the compiler, so unit data and beta stay in SGPRs
@@ -303,7 +320,10 @@ __global__ void __launch_bounds__(64 * kSynthWaves, (synth_waves<LP, FW>())) k_l
             keep_branch();                                       \
             join(JH);                                            \
         }                                                        \
-        synth_steps<LP, FW, T0, T0 + 8>(s, B, Q);                \
+        if (VEC && (JH) + 8 > nj)                                \
+            synth_tail<LP, FW, T0, T0 + 8>(s, B, Q, nj - (JH));  \
+        else                                                     \
+            synth_steps<LP, FW, T0, T0 + 8>(s, B, Q);            \
     }
     __builtin_amdgcn_s_setprio(0);
     for (int js = js0; js < nj; js += kSegLen) {
@@ -335,11 +355,36 @@ __global__ void __launch_bounds__(64 * kSynthWaves, (synth_waves<LP, FW>())) k_l
     // Mirror fold: north = E + O, south = E - O.  For the adjoint of the
     // analysis the output carries (2 pi/nphi) w_i / c_m.
     const double cm = a.adjoint ? (2.0 * M_PI / P->nphi) * (m == 0 ? 1.0 : 0.5) : 1.0;
+    if constexpr (VEC) {
+        // x P_L is odd about the equator where P_L is even
+        const double gl = ((cdp)P->gamma)[base + nj - 1];
+        double2 t[FW];
+#pragma unroll
+        for (int f = 0; f < FW; f++) {
+            cdp tp = (cdp)a.top + 2 * ((long)(field0 + min(f, nf - 1)) * (P->M + 1) + m);
+            t[f] = make_double2(tp[0], tp[1]);
+        }
+#pragma unroll
+        for (int p = 0; p < LP; p++) {
+            const double xp = s.x[p] * (gl * ((nj & 1) ? s.ua[p] : s.ub[p]));
+#pragma unroll
+            for (int f = 0; f < FW; f++) {
+                if (nj & 1) {
+                    s.orr[p][f] = fma(xp, t[f].x, s.orr[p][f]);
+                    s.oi[p][f] = fma(xp, t[f].y, s.oi[p][f]);
+                } else {
+                    s.er[p][f] = fma(xp, t[f].x, s.er[p][f]);
+                    s.ei[p][f] = fma(xp, t[f].y, s.ei[p][f]);
+                }
+            }
+        }
+    }
 #pragma unroll
     for (int p = 0; p < LP; p++) {
         const int pair = pb + p * 64 + lane;
         if (pair >= npair) continue;
-        const double sc = a.adjoint ? cm * P->wfull[pair] : 1.0;
+        double sc = a.adjoint ? cm * P->wfull[pair] : 1.0;
+        if constexpr (VEC) sc = sc / sqrt((1.0 - s.x[p]) * (1.0 + s.x[p]));
         const int is = nlat - 1 - pair;
 #pragma unroll
         for (int f = 0; f < FW; f++) {
@@ -746,7 +791,7 @@ __global__ void __launch_bounds__(64 * W) k_legendre_analys(LegArgs a)
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-template <int LP, int FW>
+template <int LP, int FW, bool VEC>
 static int launch_synth_t(const LegLaunch& l, void* stream)
 {
     // (a launch's threads are counted in 32 bits: one launch unless the call
@@ -757,9 +802,9 @@ static int launch_synth_t(const LegLaunch& l, void* stream)
         // two waves per SIMD or fewer: one per workgroup (lmax 255, one
         // field: 10.2 us, with four 11.2; lmax 511: 16.2, with four 17.9)
         const int waves = (long)l.nunits * ng > 2048 ? kSynthWaves : 1;
-        LegArgs a{l.plans, l.units, l.q_off, l.f_off, l.in, l.out, l.nfields, l.adjoint, l.nunits, ng, g0, waves};
+        LegArgs a{l.plans, l.units, l.q_off, l.f_off, l.in, l.out, l.nfields, l.adjoint, l.nunits, ng, g0, waves, l.top};
         const int per_xcd = (l.nunits / kXcds * ng + waves - 1) / waves;
-        hipLaunchKernelGGL((k_legendre_synth<LP, FW>), dim3(kXcds * per_xcd), dim3(64 * waves), 0,
+        hipLaunchKernelGGL((k_legendre_synth<LP, FW, VEC>), dim3(kXcds * per_xcd), dim3(64 * waves), 0,
                            (hipStream_t)stream, a);
     }
     return (int)hipGetLastError();
@@ -778,11 +823,18 @@ int launch_legendre_synth(const LegLaunch& l, void* stream)
 {
     if (l.nunits <= 0) return 0;
 #define SHTN_S(LPV, FWV) \
-    if (l.lp == LPV && l.fw == FWV) return launch_synth_t<LPV, FWV>(l, stream);
+    if (l.lp == LPV && l.fw == FWV && !l.top) return launch_synth_t<LPV, FWV, false>(l, stream);
     SHTN_S(1, 1) SHTN_S(2, 1) SHTN_S(4, 1)
     SHTN_S(1, 2) SHTN_S(2, 2) SHTN_S(4, 2)
     SHTN_S(1, 4) SHTN_S(2, 4)
 #undef SHTN_S
+    // (vector transforms: the combinations an automatic tiling takes; two pairs
+    // and four fields per lane would need more registers than four waves per
+    // SIMD have)
+#define SHTN_V(LPV, FWV) \
+    if (l.lp == LPV && l.fw == FWV && l.top) return launch_synth_t<LPV, FWV, true>(l, stream);
+    SHTN_V(1, 1) SHTN_V(2, 1) SHTN_V(1, 2) SHTN_V(2, 2) SHTN_V(1, 4)
+#undef SHTN_V
     return (int)hipErrorInvalidValue;
 }
 

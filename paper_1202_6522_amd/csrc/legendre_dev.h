@@ -44,6 +44,9 @@ struct LegArgs {
     // synthesis: field groups (of FW fields) of this launch, and the first one
     int groups, group0;
     int waves;  // synthesis: waves per workgroup
+    // vector transforms: per (field, order) the coefficient of x P_L (synthesis),
+    // or the sum with x P_L (analysis), at 2 (f (M+1) + m)
+    double* top = nullptr;
 };
 
 __device__ __forceinline__ long field_q_off(const LegArgs& a, int f, long nlm)

@@ -327,6 +327,7 @@ struct LegLaunch {
     int adjoint;           // 0 forward transform, 1 adjoint variant
     int lp, fw;            // template selection
     int waves = 1;         // analysis: waves per unit (latitude pairs 64 lp waves)
+    double* top = nullptr; // vector transforms: the terms with x P_L (see vector.hip), else null
 };
 // Stored-P kernels (ptable.hip).
 struct PtabArgs {
@@ -349,6 +350,10 @@ int launch_sp_analys(const PtabArgs& a, int M, int nbr_max, int jt, int ct, void
 // the scalar stages.
 int launch_vec_spec_in(const DevPlan* plan, int L, int M, const double* S, const double* T, double* Q4, int nfields,
                        int nn, void* stream);
+int launch_vec_spread(const DevPlan* plan, int L, int M, const double* S, const double* T, double* Q2, double* top,
+                      int nfields, int nn, void* stream);
+int launch_vec_gather(const DevPlan* plan, int L, int M, const double* A2, const double* top, double* S, double* T,
+                      int nfields, int nn, void* stream);
 int launch_vec_f_out(const DevPlan* plan, long f_size, const double* F4, double* Fv, int nfields, void* stream);
 int launch_vec_f_in(const DevPlan* plan, long f_size, const double* Fv, double* F4, int nfields, void* stream);
 int launch_vec_spec_out(const DevPlan* plan, int L, int M, const double* A4, double* S, double* T, int nfields,
@@ -369,11 +374,19 @@ inline int mf_fields(int npair, long nlm, int nfields)
                  eight = npair <= 1024 ? (nfields + 7) / 8 * 6.1 : vec + four;
     return vec <= four && vec <= eight ? 0 : (eight <= four ? 8 : 4);
 }
-// Waves of a unit (each covers 256 latitude pairs with four fields, 128 with eight).
+// Fields per unit of a vector analysis of nfields components, which always
+// runs there: one vector field takes a unit of its own two components.
+inline int mf_vec_fields(int npair, int nfields)
+{
+    if (nfields == 2) return 2;
+    const double four = (nfields + 3) / 4 * 3.45, eight = npair <= 1024 ? (nfields + 7) / 8 * 6.1 : 2 * four;
+    return eight <= four ? 8 : 4;
+}
+// Waves of a unit (each covers 256 latitude pairs with up to four fields, 128 with eight).
 inline int mf_waves(int npair, int fields)
 {
     int w = 1;
-    while (1024 / fields * w < npair) w *= 2;
+    while ((fields == 8 ? 128 : 256) * w < npair) w *= 2;
     return w;
 }
 int launch_legendre_analys_mf(const LegLaunch& a, int npair, int fields, void* stream);
@@ -391,6 +404,7 @@ struct FftLaunch {
     const long* f_off;        // per-field F offset (doubles) or null
     const double* in;
     double* out;
+    double* grid2 = nullptr;  // not null: fields 2 f have grid f of the grid pointer, fields 2 f + 1 grid f here
     int nfields;
     double scale;             // r2c: output scale (2 pi/nphi or 1)
     int uniform_k = 0;        // 1: every row of the launch has K points

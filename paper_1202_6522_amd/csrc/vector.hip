@@ -18,6 +18,22 @@
 // k_vec_spec_out.  sin(theta) is taken as sqrt((1-x)(1+x)) of the node x the
 // Legendre stage uses.
 //
+// On the fly, the products with x are taken out of the sums: x P_n =
+// a_{n+1} P_{n+1} + a_n P_{n-1}, a_n = c_n/(2n+1), for n < L, so that two
+// spectra per field are enough,
+//   sin Vt_m = Syn(B) + L S_L x P_L,
+//   B_n = (n-1) a_n S_{n-1} - (n+2) a_{n+1} S_{n+1} - i m T_n
+// (at n = L-1 the term with S_L is -c_L S_L, that of L S_L x P_L being apart),
+// and likewise for Vp with T and -S; and two analyses,
+//   n(n+1) S_n = n a_{n+1} A(Ft/s)_{n+1} - (n+1) a_n A(Ft/s)_{n-1} - i m A(Fp/s)_n
+// (at n = L: L A(x Ft/s)_L - c_L A(Ft/s)_{L-1}).  The Legendre kernels take the
+// terms with x P_L and the division by sin along (`top`); k_vec_spread and
+// k_vec_gather form the spectra.  Fields are interleaved: component theta of
+// field f is scalar field 2 f, phi 2 f + 1.  (Against the four scalar passes:
+// one field at lmax 1023, synthesis and analysis, 342 us and 237; four fields at
+// lmax 255 80 and 56.)  Stored tables and tilings set by the caller take
+// the four passes.
+//
 // Adjoints (the same kernels, `nn` selects the n(n+1) scaling): the
 // transpose of the synthesis is the analysis combination without the
 // division by n(n+1), fed by the scalar stages in their adjoint mode (unit
@@ -73,6 +89,79 @@ __global__ void __launch_bounds__(256) k_vec_spec_in(const DevPlan* plan, const 
     q[nlm + i] = make_double2(c * sn.x - dm * t.y, c * sn.y + dm * t.x);
     q[2 * nlm + i] = make_double2(dn * t.x, dn * t.y);
     q[3 * nlm + i] = make_double2(c * tn.x + dm * s.y, c * tn.y - dm * s.x);
+}
+
+// Q2[2f], Q2[2f + 1] and their terms with x P_L from S[f], T[f] (see above),
+// with nn divided by n(n+1) first.  One thread per (degree, order, field).
+__global__ void __launch_bounds__(256) k_vec_spread(const DevPlan* plan, const double* S, const double* T,
+                                                    double* Q2, double* top, int nfields, int nn)
+{
+    const DevPlan& P = *plan;
+    const int m = blockIdx.y, f = blockIdx.z;
+    const int n = m + blockIdx.x * 256 + threadIdx.x;
+    const int L = P.L;
+    if (n > L || f >= nfields) return;
+    const long nlm = P.nlm;
+    const long i = vec_base(L, m) + (n - m);
+    const double2* s2 = (const double2*)(S + 2 * (long)f * nlm);
+    const double2* t2 = (const double2*)(T + 2 * (long)f * nlm);
+    const double2 zero = make_double2(0.0, 0.0);
+    const double2 s = s2[i], t = t2[i];
+    const double2 sl = n > m ? s2[i - 1] : zero, tl = n > m ? t2[i - 1] : zero;
+    const double2 su = n < L ? s2[i + 1] : zero, tu = n < L ? t2[i + 1] : zero;
+    const double w0 = nn ? inv_nn(n) : 1.0;
+    double lo = n > m ? (n - 1) * (vec_c(n, m) / (2 * n + 1)) : 0.0, up = 0.0;
+    if (n < L) {
+        const double c = vec_c(n + 1, m);
+        up = n + 1 < L ? -(n + 2) * (c / (2 * n + 3)) : -c;
+    }
+    if (nn) {
+        lo *= inv_nn(n - 1);
+        up *= inv_nn(n + 1);
+    }
+    const double dm = m * w0;
+    double2* q = (double2*)(Q2 + 2 * (long)(2 * f) * nlm);
+    q[i] = make_double2(lo * sl.x + up * su.x + dm * t.y, lo * sl.y + up * su.y - dm * t.x);
+    q[nlm + i] = make_double2(lo * tl.x + up * tu.x - dm * s.y, lo * tl.y + up * tu.y + dm * s.x);
+    if (n == L) {
+        const double w = L * w0;
+        double2* tp = (double2*)top + (long)(2 * f) * (P.M + 1) + m;
+        tp[0] = make_double2(w * s.x, w * s.y);
+        tp[P.M + 1] = make_double2(w * t.x, w * t.y);
+    }
+}
+
+// S, T from the two analyses A2[2f + k] (k: Ft/s, Fp/s) and their sums with
+// x P_L (see above), divided by n(n+1) when nn; 0 at degree 0.
+__global__ void __launch_bounds__(256) k_vec_gather(const DevPlan* plan, const double* A2, const double* top,
+                                                    double* S, double* T, int nfields, int nn)
+{
+    const DevPlan& P = *plan;
+    const int m = blockIdx.y, f = blockIdx.z;
+    const int n = m + blockIdx.x * 256 + threadIdx.x;
+    const int L = P.L;
+    if (n > L || f >= nfields) return;
+    const long nlm = P.nlm;
+    const long i = vec_base(L, m) + (n - m);
+    const double2* a = (const double2*)(A2 + 2 * (long)(2 * f) * nlm);
+    const double2* tp = (const double2*)top + (long)(2 * f) * (P.M + 1) + m;
+    const double2 zero = make_double2(0.0, 0.0);
+    const double2 t = a[i], p = a[nlm + i];
+    const double2 tl = n > m ? a[i - 1] : zero, pl = n > m ? a[nlm + i - 1] : zero;
+    const double2 tu = n < L ? a[i + 1] : tp[0], pu = n < L ? a[nlm + i + 1] : tp[P.M + 1];
+    const double c = vec_c(n, m);
+    const double up = n < L ? n * (vec_c(n + 1, m) / (2 * n + 3)) : (double)L;
+    const double lo = n < L ? (n + 1) * (c / (2 * n + 1)) : c;
+    const double inv = n == 0 ? 0.0 : (nn ? inv_nn(n) : 1.0);
+    const double dm = m;
+    double2 sv = make_double2((up * tu.x - lo * tl.x + dm * p.y) * inv, (up * tu.y - lo * tl.y - dm * p.x) * inv);
+    double2 tv = make_double2((up * pu.x - lo * pl.x - dm * t.y) * inv, (up * pu.y - lo * pl.y + dm * t.x) * inv);
+    if (m == 0) {
+        sv.y = 0.0;
+        tv.y = 0.0;
+    }
+    ((double2*)(S + 2 * (long)f * nlm))[i] = sv;
+    ((double2*)(T + 2 * (long)f * nlm))[i] = tv;
 }
 
 // Latitude and order of the e-th complex entry of a field's F (tiles of
@@ -174,6 +263,22 @@ int launch_vec_spec_in(const DevPlan* plan, int L, int M, const double* S, const
 {
     hipLaunchKernelGGL(k_vec_spec_in, dim3((L + 256) / 256, M + 1, nfields), dim3(256), 0, (hipStream_t)stream,
                        plan, S, T, Q4, nfields, nn);
+    return (int)hipGetLastError();
+}
+
+int launch_vec_spread(const DevPlan* plan, int L, int M, const double* S, const double* T, double* Q2, double* top,
+                      int nfields, int nn, void* stream)
+{
+    hipLaunchKernelGGL(k_vec_spread, dim3((L + 256) / 256, M + 1, nfields), dim3(256), 0, (hipStream_t)stream, plan,
+                       S, T, Q2, top, nfields, nn);
+    return (int)hipGetLastError();
+}
+
+int launch_vec_gather(const DevPlan* plan, int L, int M, const double* A2, const double* top, double* S, double* T,
+                      int nfields, int nn, void* stream)
+{
+    hipLaunchKernelGGL(k_vec_gather, dim3((L + 256) / 256, M + 1, nfields), dim3(256), 0, (hipStream_t)stream, plan,
+                       A2, top, S, T, nfields, nn);
     return (int)hipGetLastError();
 }
 
