@@ -105,7 +105,7 @@ int sp_args(const Plan& p, const double* in, double* out, int nfields, int adjoi
 {
     if (!p.ptab.built) return fail(SHTN_ESTATE, "stored-P table not built for the current plan (shtn_ptable_build)");
     a = PtabArgs{dplan(p), (const long*)p.ptab.dev, (const double*)((char*)p.ptab.dev + p.ptab.head_bytes),
-                 in, out, nfields, adjoint, p.ptab.npt, 0};
+                 in, out, nfields, adjoint, p.ptab.npt};
     return SHTN_OK;
 }
 
@@ -121,7 +121,7 @@ int leg_to_f(const Plan& p, const double* Q, double* F, int nfields, int adjoint
         if (rc) return rc;
         {
             ProfScope ps(PK_LEG_SYNTH, stream);
-            e = launch_sp_synth(a, p.M, p.ptab.synth_rt, p.ptab.synth_ct, stream);
+            e = launch_sp_synth(a, p.M, p.ptab.rt(), p.ptab.synth_ct, stream);
         }
         if (e) return hip_fail(e, "stored-P synthesis launch");
         return SHTN_OK;
@@ -210,10 +210,9 @@ int f_to_leg(const Plan& p, const double* F, double* Q, int nfields, int adjoint
         PtabArgs a;
         int rc = sp_args(p, F, Q, nfields, adjoint, a);
         if (rc) return rc;
-        const int nbr_max = ((p.L + 2) / 2 + 15) / 16;  // block rows of order 0, even parity
         {
             ProfScope ps(PK_LEG_ANALYS, stream);
-            e = launch_sp_analys(a, p.M, nbr_max, p.ptab.analys_jt, p.ptab.analys_ct, stream);
+            e = launch_sp_analys(a, p.L, p.M, p.ptab.jt(), p.ptab.analys_ct, stream);
         }
         if (e) return hip_fail(e, "stored-P analysis launch");
         return SHTN_OK;
@@ -764,6 +763,7 @@ int shtn_ptable_set_tiling(shtn_plan_t plan, int synth_rt, int synth_ct, int ana
     if (!ok_t(synth_rt) || !ok_t(analys_jt)) return fail(SHTN_EINVAL, "synth_rt and analys_jt must be 1, 2 or 4");
     if (!ok_c(synth_ct) || !ok_c(analys_ct)) return fail(SHTN_EINVAL, "synth_ct and analys_ct must be 1 or 2");
     PTable& t = plan->p->ptab;
+    t.auto_tiles = false;
     t.synth_rt = synth_rt;
     t.synth_ct = synth_ct;
     t.analys_jt = analys_jt;

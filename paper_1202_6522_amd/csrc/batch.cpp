@@ -348,16 +348,16 @@ int run_stored(const shtn_batch_s& b, const double* in, double* out, int synth, 
     for (const auto& r : b.stored_runs) {
         const Plan& p = *b.plans[r[0]];
         PtabArgs a{plans + r[0], (const long*)p.ptab.dev,
-                   (const double*)((const char*)p.ptab.dev + p.ptab.head_bytes), in, out, r[2], 0, p.ptab.npt, 0};
+                   (const double*)((const char*)p.ptab.dev + p.ptab.head_bytes), in, out, r[2], 0, p.ptab.npt};
         a.q_off = dev_at<const long>(b, b.off_q) + r[1];
         a.f_off = dev_at<const long>(b, b.off_f) + r[1];
         int e;
         if (synth) {
             ProfScope ps(PK_LEG_SYNTH, stream);
-            e = launch_sp_synth(a, p.M, p.ptab.synth_rt, p.ptab.synth_ct, stream);
+            e = launch_sp_synth(a, p.M, p.ptab.rt(), p.ptab.synth_ct, stream);
         } else {
             ProfScope ps(PK_LEG_ANALYS, stream);
-            e = launch_sp_analys(a, p.M, ((p.L + 2) / 2 + 15) / 16, p.ptab.analys_jt, p.ptab.analys_ct, stream);
+            e = launch_sp_analys(a, p.L, p.M, p.ptab.jt(), p.ptab.analys_ct, stream);
         }
         if (e) return hip_error(e, "batch stored-P launch");
     }

@@ -32,18 +32,72 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // m-major index of (n = m, m): the first coefficient of order m.
 __device__ __forceinline__ long order_base(int L, int m) { return (long)m * (2 * L + 1 - m) / 2 + m; }
 
-// XCD-aware placement: workgroup b of a launch runs on XCD b % kXcds.  The
-// nu units of order m all go to XCD m % kXcds, one after another in that
-// XCD's share of the launch (orders ascending, longest first), so they share
-// its L2 for the order's inputs.  False past the last order.
+// A workgroup of the two passes is kSpWaves waves of one order: they share the
+// order's inputs, which the workgroup puts in LDS.
+constexpr int kSpWaves = 4;
+constexpr int kXcdCus = 32;
+
+// XCD-aware placement: workgroup b of a launch runs on XCD b % kXcds, and an
+// XCD's workgroups go to its CUs in turn.  The nu workgroups of order m all go
+// to XCD m % kXcds, one after another in that XCD's share of the launch
+// (orders ascending, longest first); every second run of 32 is taken
+// backwards, so that a CU gets long and short ones.  False past the last
+// order.
+__device__ __forceinline__ int xcd_slot()
+{
+    const int slot = blockIdx.x / kXcds;
+    const int lo = slot & ~(kXcdCus - 1), n = gridDim.x / kXcds;
+    return (slot & kXcdCus) && lo + kXcdCus <= n ? 2 * lo + kXcdCus - 1 - slot : slot;
+}
 __device__ __forceinline__ bool xcd_unit(int nu, int M, int& u, int& m)
 {
-    const int b = blockIdx.x;
-    const int slot = b / kXcds;
+    const int slot = xcd_slot();
     const int k = slot / nu;
     u = slot - k * nu;
-    m = b % kXcds + kXcds * k;
+    m = blockIdx.x % kXcds + kXcds * k;
     return m <= M;
+}
+
+// Workgroup p of XCD x's queue where order m = x + 8 k has ceil((L+1-m) / w)
+// of them (w degrees each): the orders with n are consecutive, so the search
+// takes one step per n.  False past the last.
+__device__ __forceinline__ bool xcd_unit_of(int p, int w, int L, int M, int& u, int& m)
+{
+    const int x = blockIdx.x % kXcds;
+    int k0 = 0;
+    const int all = x <= M ? (M - x) / kXcds + 1 : 0;  // orders of this XCD
+    for (int n = (L + w - x) / w; n > 0 && k0 < all; n--) {
+        // orders with n or more
+        const int k1 = min(all, (L + 1 - x - w * (n - 1) + kXcds - 1) / kXcds);
+        const int c = (k1 - k0) * n;
+        if (p < c) {
+            const int k = p / n;
+            u = p - k * n;
+            m = x + kXcds * (k0 + k);
+            return true;
+        }
+        p -= c;
+        k0 = k1;
+    }
+    return false;
+}
+
+// One 16 x 16 tile of inputs per parity and column tile in LDS, one row per
+// contraction index; two of each, one read while the other is written.  Rows
+// 144 bytes apart: the complex values written by the lanes of a column fall in
+// different banks, and so (but for one of 16 columns) do the four rows read at
+// once.
+constexpr int kBRow = 18;
+template <int CT>
+using BTiles = double[2][2][CT][16 * kBRow];
+
+// The workgroup's LDS writes are seen after this; loads from global memory
+// stay in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 __device__ __forceinline__ int ptab_in_block(int jl, int pl)
@@ -102,24 +156,34 @@ __global__ void __launch_bounds__(64) k_ptable_build(const DevPlan* plan, const 
 }
 
 // ---------------------------------------------------------------------------
-// Synthesis (or the adjoint of the analysis): one wave per (order, group of
-// RT pair tiles, group of CT column tiles).  Lane l feeds A[pair l%16][degree
-// l/16] and B[degree l/16][column l%16] and holds D[pair l/16 + 4 r][column
-// l%16], r < 4.  Even and odd degrees accumulate apart; the fold north =
-// E + O, south = E - O is then lane-local.
+// Synthesis (or the adjoint of the analysis): one workgroup per (order, group
+// of kSpWaves RT pair tiles, group of CT column tiles), RT pair tiles per wave.
+// Lane l feeds A[pair l%16][degree l/16] and B[degree l/16][column l%16] and
+// holds D[pair l/16 + 4 r][column l%16], r < 4.  Even and odd degrees accumulate
+// apart; the fold north = E + O, south = E - O is then lane-local.
+//
+// Bound by the table's bytes, read once per 16 fields: 268 MB at lmax 511, 50
+// us at the rate of a plain read of as much.  The order's coefficients go
+// through LDS once per workgroup instead of through L2 once per wave, and the
+// table past the caches, which it would sweep clear of them.  16 fields at lmax
+// 511: 71.5 us (waves that read their own coefficients and waited for
+// each block's operands: 104.9).
 // ---------------------------------------------------------------------------
 template <int RT, int CT>
-__global__ void __launch_bounds__(64) k_sp_synth(PtabArgs a)
+__global__ void __launch_bounds__(64 * kSpWaves, 2) k_sp_synth(PtabArgs a)
 {
+    __shared__ __attribute__((aligned(16))) BTiles<CT> bt;
     const DevPlan& P = *a.plan;
     const int npg = (a.npt + RT - 1) / RT;
     int pg, m;
-    if (!xcd_unit(npg, P.M, pg, m)) return;
+    if (!xcd_unit((npg + kSpWaves - 1) / kSpWaves, P.M, pg, m)) return;
+    const int tid = threadIdx.x;
+    pg = pg * kSpWaves + __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L = P.L, nlat = P.nlat, npair = P.npair;
     const int npt = a.npt;
     const int nj = L - m + 1;
     const long base = order_base(L, m);
-    const int lane = threadIdx.x;
+    const int lane = tid & 63;
     const int col = lane & 15, kk = lane >> 4;
     const int comp = col & 1;
 
@@ -127,7 +191,6 @@ __global__ void __launch_bounds__(64) k_sp_synth(PtabArgs a)
     // before the first store: the output may alias them for all the compiler
     // knows, so reads placed between the stores would each wait on memory.
     const long ts = P.f_ts;
-    const double* qp[CT];
     double* fo[CT];
     bool fv[CT];
 #pragma unroll
@@ -135,14 +198,24 @@ __global__ void __launch_bounds__(64) k_sp_synth(PtabArgs a)
         const int f = (blockIdx.y * CT + c) * 8 + (col >> 1);
         fv[c] = f < a.nfields;
         const int fc = fv[c] ? f : 0;
-        qp[c] = a.in + (a.q_off ? a.q_off[fc] : (long)fc * 2 * P.nlm) + 2 * base + comp;
         fo[c] = a.out + (a.f_off ? a.f_off[fc] : (long)fc * 2 * P.f_size) + comp;
     }
-    // pair tiles past the last one read tile pg RT (always present): their
-    // output rows are never stored
+    // the coefficients this thread puts in LDS: degree 32 br + lj of one field
+    // per column tile
+    const int lj = tid & 31, lf = tid >> 5;
+    const double2* qs[CT];
+#pragma unroll
+    for (int c = 0; c < CT; c++) {
+        const int f = (blockIdx.y * CT + c) * 8 + lf;
+        const int fc = f < a.nfields ? f : 0;
+        qs[c] = (const double2*)(a.in + (a.q_off ? a.q_off[fc] : (long)fc * 2 * P.nlm)) + base;
+    }
+    // pair tiles past the last one read tile pg RT (or, in a wave past the
+    // last, the last group's): their output rows are never stored
+    const int pgc = min(pg, npg - 1);
     int tr[RT];
 #pragma unroll
-    for (int r = 0; r < RT; r++) tr[r] = pg * RT + r < npt ? r : 0;
+    for (int r = 0; r < RT; r++) tr[r] = pgc * RT + r < npt ? r : 0;
     const int a_off = ptab_in_block(kk, lane & 15);  // + 64 s for step s of a block
 
     d4 acc[2][RT][CT];
@@ -153,61 +226,76 @@ __global__ void __launch_bounds__(64) k_sp_synth(PtabArgs a)
 #pragma unroll
             for (int c = 0; c < CT; c++) acc[q][r][c] = d4{0.0, 0.0, 0.0, 0.0};
 
-    // Step br covers block row br of both parities (the odd parity has as
-    // many rows as the even one, or one fewer: its missing row reloads the
-    // even row).  All operands of a step are loaded before its first matrix
-    // instruction, every load unconditional from a valid address (one memory
-    // round trip per step; the waves resident on a SIMD overlap them).  Only
-    // the contraction index needs a mask: degrees past the order's last
-    // (among them the whole missing odd row) get a factor 0 on B (the clamped
-    // coefficient belongs to the same order, so this can only turn an output
-    // that already involves a non-finite input into NaN; every table entry is
-    // finite).  Operands of pair rows past the last and of field columns past
+    // A block row (32 degrees) is two steps, one per parity (the odd parity has
+    // as many rows as the even one, or one fewer: its missing row reloads the
+    // even row).  The table's operands of a step are loaded while the matrix
+    // instructions of the step before run, past the caches (each is used
+    // once), every load unconditional from a valid address.  Degrees past the
+    // order's last (among them the whole missing odd row) have coefficient 0.
+    // Operands of pair rows past the last and of field columns past
     // the last are left as loaded: they only reach outputs that are never
     // stored.
     const int nbr0 = (((nj + 1) >> 1) + 15) >> 4, nbr1 = ((nj >> 1) + 15) >> 4;
-    const double* t0 = a.tab + a.boff[2 * m] * 256 + (long)pg * RT * 256 + a_off;
-    const double* t1 = a.tab + a.boff[2 * m + 1] * 256 + (long)pg * RT * 256 + a_off;
+    const double* t0 = a.tab + a.boff[2 * m] * 256 + (long)pgc * RT * 256 + a_off;
+    const double* t1 = a.tab + a.boff[2 * m + 1] * 256 + (long)pgc * RT * 256 + a_off;
     struct Ops {
-        double a[2][4][RT];
-        double b[2][4][CT];
+        double a[4][RT];
     };
-    auto load = [&](Ops& o, int br) {
+    auto load = [&](Ops& o, int br, int q) {
+        const double* tb = (q && br < nbr1 ? t1 : t0) + (long)br * npt * 256;
 #pragma unroll
-        for (int q = 0; q < 2; q++) {
-            const double* tb = (q && br < nbr1 ? t1 : t0) + (long)br * npt * 256;
+        for (int s = 0; s < 4; s++)
 #pragma unroll
-            for (int s = 0; s < 4; s++) {
+            for (int r = 0; r < RT; r++) o.a[s][r] = __builtin_nontemporal_load(tb + tr[r] * 256 + s * 64);
+        // (the loads stay ahead of the matrix instructions that follow)
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    double2 qv[CT];
+    auto load_q = [&](int br) {
+        const int j = min(32 * br + lj, nj - 1);
 #pragma unroll
-                for (int r = 0; r < RT; r++) o.a[q][s][r] = tb[tr[r] * 256 + s * 64];
-                const int j = min(2 * (br * 16 + s * 4 + kk) + q, nj - 1);
+        for (int c = 0; c < CT; c++) qv[c] = qs[c][j];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto put_q = [&](int br) {
+        const bool in = 32 * br + lj < nj;
 #pragma unroll
-                for (int c = 0; c < CT; c++) o.b[q][s][c] = qp[c][2 * j];
-            }
+        for (int c = 0; c < CT; c++)
+            *(double2*)&bt[br & 1][lj & 1][c][(lj >> 1) * kBRow + 2 * lf] =
+                make_double2(in ? qv[c].x : 0.0, in ? qv[c].y : 0.0);
+    };
+    auto run = [&](const Ops& o, int br, int q) {
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            double bv[CT];
+#pragma unroll
+            for (int c = 0; c < CT; c++) bv[c] = bt[br & 1][q][c][(4 * s + kk) * kBRow + col];
+#pragma unroll
+            for (int r = 0; r < RT; r++)
+#pragma unroll
+                for (int c = 0; c < CT; c++)
+                    acc[q][r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a[s][r], bv[c], acc[q][r][c], 0, 0, 0);
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
-    auto run = [&](const Ops& o, int br) {
-#pragma unroll
-        for (int q = 0; q < 2; q++) {
-#pragma unroll
-            for (int s = 0; s < 4; s++) {
-                const double mj = 2 * (br * 16 + s * 4 + kk) + q < nj ? 1.0 : 0.0;
-                double bv[CT];
-#pragma unroll
-                for (int c = 0; c < CT; c++) bv[c] = o.b[q][s][c] * mj;
-#pragma unroll
-                for (int r = 0; r < RT; r++)
-#pragma unroll
-                    for (int c = 0; c < CT; c++)
-                        acc[q][r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a[q][s][r], bv[c], acc[q][r][c], 0, 0, 0);
-            }
-        }
-    };
-    for (int br = 0; br < nbr0; br++) {
-        Ops o;
-        load(o, br);
-        run(o, br);
+    Ops even, odd;
+    load_q(0);
+    load(even, 0, 0);
+    put_q(0);
+    lds_barrier();
+    for (int br = 0; br < nbr0 - 1; br++) {
+        load_q(br + 1);
+        load(odd, br, 1);
+        run(even, br, 0);
+        load(even, br + 1, 0);
+        run(odd, br, 1);
+        put_q(br + 1);
+        lds_barrier();
     }
+    load(odd, nbr0 - 1, 1);
+    run(even, nbr0 - 1, 0);
+    run(odd, nbr0 - 1, 1);
+    if (pg >= npg) return;
 
     // For the adjoint of the analysis the output carries (2 pi/nphi) w_i / c_m.
     const double cm = a.adjoint ? (2.0 * M_PI / P.nphi) * (m == 0 ? 1.0 : 0.5) : 1.0;
@@ -236,31 +324,38 @@ __global__ void __launch_bounds__(64) k_sp_synth(PtabArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Analysis (or the adjoint of the synthesis): one wave per (order, group of
-// JT block rows of each parity, group of CT column tiles); the contraction
-// runs over all pairs, 4 per step.  Lane l feeds A[degree l%16][pair l/16]
-// and B[pair l/16][column l%16] = the folded, weighted longitude
-// coefficients, and holds D[degree l/16 + 4 r][column l%16].
+// Analysis (or the adjoint of the synthesis): one workgroup per (order, group
+// of kSpWaves JT block rows of each parity, group of CT column tiles), JT block
+// rows per wave; the contraction runs over all pairs, 4 per matrix
+// instruction.  Lane l feeds A[degree l%16][pair l/16] and B[pair l/16][column
+// l%16] = the folded, weighted longitude coefficients, and holds D[degree l/16
+// + 4 r][column l%16].
+//
+// Bound as the synthesis is; the longitude coefficients are folded once per
+// workgroup.  16 fields at lmax 511: 84.6 us (waves on their own: 123.2; with
+// two buffers of operands 110, and the more waves of different orders ran side
+// by side the slower, 131: their inputs then no longer fit the caches).
 // ---------------------------------------------------------------------------
 template <int JT, int CT>
-__global__ void __launch_bounds__(64) k_sp_analys(PtabArgs a)
+__global__ void __launch_bounds__(64 * kSpWaves, 2) k_sp_analys(PtabArgs a)
 {
+    __shared__ __attribute__((aligned(16))) BTiles<CT> bt;
     const DevPlan& P = *a.plan;
     int g, m;
-    if (!xcd_unit(a.nu, P.M, g, m)) return;
+    if (!xcd_unit_of(xcd_slot(), 32 * JT * kSpWaves, P.L, P.M, g, m)) return;
+    const int tid = threadIdx.x;
+    g = g * kSpWaves + __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L = P.L, nlat = P.nlat, npair = P.npair;
     const int npt = a.npt;
     const int nj = L - m + 1;
     const int nbr0 = (((nj + 1) >> 1) + 15) >> 4, nbr1 = ((nj >> 1) + 15) >> 4;
-    if (g * JT >= nbr0) return;  // nbr0 >= nbr1
     const long base = order_base(L, m);
-    const int lane = threadIdx.x;
+    const int lane = tid & 63;
     const int col = lane & 15, kk = lane >> 4;
     const int comp = col & 1;
 
     // Output bases are read here, before the first store (which, for all the
     // compiler knows, may alias them).
-    const double* fp[CT];
     double* qo[CT];
     bool fv[CT];
 #pragma unroll
@@ -268,7 +363,6 @@ __global__ void __launch_bounds__(64) k_sp_analys(PtabArgs a)
         const int f = (blockIdx.y * CT + c) * 8 + (col >> 1);
         fv[c] = f < a.nfields;
         const int fc = fv[c] ? f : 0;
-        fp[c] = a.in + (a.f_off ? a.f_off[fc] : (long)fc * 2 * P.f_size) + comp;
         qo[c] = a.out + (a.q_off ? a.q_off[fc] : (long)fc * 2 * P.nlm) + 2 * base + comp;
     }
     bool rv[2][JT];
@@ -285,6 +379,17 @@ __global__ void __launch_bounds__(64) k_sp_analys(PtabArgs a)
             const long blk = rv[q][t] ? a.boff[2 * m + q] + (long)br * npt : a.boff[2 * m];
             tq[q][t] = a.tab + blk * 256 + ptab_in_block(lane & 15, kk);  // + 256 pt + 16 (step % 4)
         }
+    // the coefficients this thread puts in LDS, folded and weighted: pair
+    // 16 pt + lp of one field (8 CT fields: with one column tile half of the
+    // workgroup)
+    const int lp = tid & 15, lf = tid >> 4;
+    const bool loads = lf < 8 * CT;
+    const double2* fp;
+    {
+        const int f = blockIdx.y * CT * 8 + lf;
+        const int fc = f < a.nfields && loads ? f : 0;
+        fp = (const double2*)(a.in + (a.f_off ? a.f_off[fc] : (long)fc * 2 * P.f_size));
+    }
 
     d4 acc[2][JT][CT];
 #pragma unroll
@@ -294,49 +399,82 @@ __global__ void __launch_bounds__(64) k_sp_analys(PtabArgs a)
 #pragma unroll
             for (int c = 0; c < CT; c++) acc[q][t][c] = d4{0.0, 0.0, 0.0, 0.0};
 
-    // Per pair tile (4 steps of 4 pairs) every operand is loaded before the
-    // first matrix instruction, unconditionally from valid addresses (pairs
-    // past the last read the last pair with weight 0): one memory round trip
-    // per tile, overlapped across the waves resident on a SIMD.
-    for (int pt = 0; pt < npt; pt++) {
-        double pa[4][2][JT], vn[4][CT], vs[4][CT], wv[4];
+    // A pair tile is two steps of 2 x 4 pairs.  The table's operands of a step
+    // are loaded while the matrix instructions of the step before run, past
+    // the caches (each is used once), unconditionally from
+    // valid addresses (pairs past the last read the last pair with weight 0).
+    struct Ops {
+        double pa[2][2][JT];
+    };
+    auto load = [&](Ops& o, int pt, int hf) {
 #pragma unroll
-        for (int s = 0; s < 4; s++) {
-            const int pc = min(pt * 16 + s * 4 + kk, npair - 1);
-            wv[s] = P.wq[pc];
-#pragma unroll
-            for (int c = 0; c < CT; c++) {
-                vn[s][c] = fp[c][2 * f_index(P.f_ts, m, pc)];
-                vs[s][c] = fp[c][2 * f_index(P.f_ts, m, nlat - 1 - pc)];
-            }
+        for (int i = 0; i < 2; i++)
 #pragma unroll
             for (int q = 0; q < 2; q++)
 #pragma unroll
-                for (int t = 0; t < JT; t++) pa[s][q][t] = tq[q][t][pt * 256 + s * 16];
-        }
-        // keep every load of the tile ahead of its matrix instructions: left
-        // alone, the scheduler interleaves them with one wait per group
+                for (int t = 0; t < JT; t++)
+                    o.pa[i][q][t] = __builtin_nontemporal_load(tq[q][t] + pt * 256 + (2 * hf + i) * 16);
+        // (the loads stay ahead of the matrix instructions that follow)
         __builtin_amdgcn_sched_barrier(0);
+    };
+    double2 vn, vs;
+    double wv;
+    auto load_f = [&](int pt) {
+        const int pc = min(pt * 16 + lp, npair - 1);
+        wv = P.wq[pc];
+        vn = fp[f_index(P.f_ts, m, pc)];
+        vs = fp[f_index(P.f_ts, m, nlat - 1 - pc)];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto put_f = [&](int pt) {
+        const int pair = pt * 16 + lp;
+        const bool middle = (nlat & 1) && pair == npair - 1;
+        const double wt = pair >= npair ? 0.0 : (a.adjoint ? (middle ? 0.5 : 1.0) : wv);
+        if (loads) {
+            const int o = lp * kBRow + 2 * (lf & 7);
+            *(double2*)&bt[pt & 1][0][lf >> 3][o] = make_double2(wt * (vn.x + vs.x), wt * (vn.y + vs.y));
+            *(double2*)&bt[pt & 1][1][lf >> 3][o] = make_double2(wt * (vn.x - vs.x), wt * (vn.y - vs.y));
+        }
+    };
+    auto run = [&](const Ops& o, int pt, int hf) {
 #pragma unroll
-        for (int s = 0; s < 4; s++) {
-            const int pair = pt * 16 + s * 4 + kk;
-            const bool middle = (nlat & 1) && pair == npair - 1;
-            const double wt = pair >= npair ? 0.0 : (a.adjoint ? (middle ? 0.5 : 1.0) : wv[s]);
-            double ge[CT], go[CT];
+        for (int i = 0; i < 2; i++) {
+            double bv[2][CT];
 #pragma unroll
-            for (int c = 0; c < CT; c++) {
-                ge[c] = wt * (vn[s][c] + vs[s][c]);
-                go[c] = wt * (vn[s][c] - vs[s][c]);
-            }
+            for (int q = 0; q < 2; q++)
+#pragma unroll
+                for (int c = 0; c < CT; c++) bv[q][c] = bt[pt & 1][q][c][(4 * (2 * hf + i) + kk) * kBRow + col];
 #pragma unroll
             for (int t = 0; t < JT; t++)
 #pragma unroll
                 for (int c = 0; c < CT; c++) {
-                    acc[0][t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(pa[s][0][t], ge[c], acc[0][t][c], 0, 0, 0);
-                    acc[1][t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(pa[s][1][t], go[c], acc[1][t][c], 0, 0, 0);
+                    acc[0][t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.pa[i][0][t], bv[0][c], acc[0][t][c], 0, 0, 0);
+                    acc[1][t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.pa[i][1][t], bv[1][c], acc[1][t][c], 0, 0, 0);
                 }
         }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const bool any = g * JT < nbr0;  // else this wave only helps with the inputs
+    Ops lo, hi;
+    load_f(0);
+    load(lo, 0, 0);
+    put_f(0);
+    lds_barrier();
+    for (int pt = 0; pt < npt - 1; pt++) {
+        load_f(pt + 1);
+        if (any) {
+            load(hi, pt, 1);
+            run(lo, pt, 0);
+            load(lo, pt + 1, 0);
+            run(hi, pt, 1);
+        }
+        put_f(pt + 1);
+        lds_barrier();
     }
+    if (!any) return;
+    load(hi, npt - 1, 1);
+    run(lo, npt - 1, 0);
+    run(hi, npt - 1, 1);
 
     const double cm = (m == 0 || !a.adjoint) ? 1.0 : 2.0;
 #pragma unroll
@@ -371,20 +509,18 @@ static int launch_sp_synth_t(const PtabArgs& a, int M, void* stream)
 {
     const int npg = (a.npt + RT - 1) / RT;
     const int nfg = (a.nfields + 8 * CT - 1) / (8 * CT);
-    const int nx = kXcds * ((M + kXcds) / kXcds) * npg;
-    hipLaunchKernelGGL((k_sp_synth<RT, CT>), dim3(nx, nfg), dim3(64), 0, (hipStream_t)stream, a);
+    const int nx = kXcds * ((M + kXcds) / kXcds) * ((npg + kSpWaves - 1) / kSpWaves);
+    hipLaunchKernelGGL((k_sp_synth<RT, CT>), dim3(nx, nfg), dim3(64 * kSpWaves), 0, (hipStream_t)stream, a);
     return (int)hipGetLastError();
 }
 
 template <int JT, int CT>
-static int launch_sp_analys_t(const PtabArgs& a, int M, int nbr_max, void* stream)
+static int launch_sp_analys_t(const PtabArgs& a, int L, int M, void* stream)
 {
-    const int ng = (nbr_max + JT - 1) / JT;
     const int nfg = (a.nfields + 8 * CT - 1) / (8 * CT);
-    const int nx = kXcds * ((M + kXcds) / kXcds) * ng;
-    PtabArgs b = a;
-    b.nu = ng;
-    hipLaunchKernelGGL((k_sp_analys<JT, CT>), dim3(nx, nfg), dim3(64), 0, (hipStream_t)stream, b);
+    int units = 0;  // workgroups of XCD 0, which has the most (see xcd_unit_of)
+    for (int m = 0; m <= M; m += kXcds) units += (L - m + 32 * JT * kSpWaves) / (32 * JT * kSpWaves);
+    hipLaunchKernelGGL((k_sp_analys<JT, CT>), dim3(kXcds * units, nfg), dim3(64 * kSpWaves), 0, (hipStream_t)stream, a);
     return (int)hipGetLastError();
 }
 
@@ -400,11 +536,11 @@ int launch_sp_synth(const PtabArgs& a, int M, int rt, int ct, void* stream)
     return (int)hipErrorInvalidValue;
 }
 
-int launch_sp_analys(const PtabArgs& a, int M, int nbr_max, int jt, int ct, void* stream)
+int launch_sp_analys(const PtabArgs& a, int L, int M, int jt, int ct, void* stream)
 {
     if (a.nfields <= 8) ct = 1;
 #define SHTN_SP(JV, CV) \
-    if (jt == JV && ct == CV) return launch_sp_analys_t<JV, CV>(a, M, nbr_max, stream);
+    if (jt == JV && ct == CV) return launch_sp_analys_t<JV, CV>(a, L, M, stream);
     SHTN_SP(1, 1) SHTN_SP(2, 1) SHTN_SP(4, 1) SHTN_SP(1, 2) SHTN_SP(2, 2) SHTN_SP(4, 2)
 #undef SHTN_SP
     return (int)hipErrorInvalidValue;

@@ -168,6 +168,14 @@ struct PTable {
     bool built = false;       // matches the plan's current lane starts
     int synth_rt = 4, synth_ct = 2;    // synthesis: pair tiles, column tiles per wave
     int analys_jt = 4, analys_ct = 2;  // analysis: block rows per parity, column tiles per wave
+    // until a decomposition is set, both run one tile per wave: the waves of a
+    // workgroup share the inputs through LDS, so more tiles per wave save no
+    // reads and leave fewer waves (16 fields, synthesis and analysis in us, 1,
+    // 2 and 4 tiles: lmax 511 71.5 and 84.6, 71.9 and 88.4, 73.2 and 90.4;
+    // lmax 255 18.7 and 22.5, 21.7 and 24.8, 31.6 and 32.8)
+    bool auto_tiles = true;
+    int rt() const { return auto_tiles ? 1 : synth_rt; }
+    int jt() const { return auto_tiles ? 1 : analys_jt; }
 };
 
 struct Plan {
@@ -339,13 +347,12 @@ struct PtabArgs {
     int nfields;
     int adjoint;
     int npt;
-    int nu;              // analysis: units (groups of block rows) per order, set by the launcher
     const long* q_off = nullptr;  // per-field spectrum offset (doubles), or null (f * 2 nlm)
     const long* f_off = nullptr;  // per-field F offset (doubles), or null (f * 2 f_size)
 };
 int launch_ptable_build(const DevPlan* plan, const long* boff, double* tab, int npt, int M, void* stream);
 int launch_sp_synth(const PtabArgs& a, int M, int rt, int ct, void* stream);
-int launch_sp_analys(const PtabArgs& a, int M, int nbr_max, int jt, int ct, void* stream);
+int launch_sp_analys(const PtabArgs& a, int L, int M, int jt, int ct, void* stream);
 // Vector transforms (vector.hip): spectral and latitude combinations around
 // the scalar stages.
 int launch_vec_spec_in(const DevPlan* plan, int L, int M, const double* S, const double* T, double* Q4, int nfields,
