@@ -121,7 +121,7 @@ int leg_to_f(const Plan& p, const double* Q, double* F, int nfields, int adjoint
         if (rc) return rc;
         {
             ProfScope ps(PK_LEG_SYNTH, stream);
-            e = launch_sp_synth(a, p.M, p.ptab.rt(), p.ptab.synth_ct, stream);
+            e = launch_sp_synth(a, p.M, p.ptab.rt(), p.ptab.sct(), stream);
         }
         if (e) return hip_fail(e, "stored-P synthesis launch");
         return SHTN_OK;
@@ -212,7 +212,7 @@ int f_to_leg(const Plan& p, const double* F, double* Q, int nfields, int adjoint
         if (rc) return rc;
         {
             ProfScope ps(PK_LEG_ANALYS, stream);
-            e = launch_sp_analys(a, p.L, p.M, p.ptab.jt(), p.ptab.analys_ct, stream);
+            e = launch_sp_analys(a, p.L, p.M, p.ptab.jt(), p.ptab.act(), stream);
         }
         if (e) return hip_fail(e, "stored-P analysis launch");
         return SHTN_OK;

@@ -354,10 +354,10 @@ int run_stored(const shtn_batch_s& b, const double* in, double* out, int synth, 
         int e;
         if (synth) {
             ProfScope ps(PK_LEG_SYNTH, stream);
-            e = launch_sp_synth(a, p.M, p.ptab.rt(), p.ptab.synth_ct, stream);
+            e = launch_sp_synth(a, p.M, p.ptab.rt(), p.ptab.sct(), stream);
         } else {
             ProfScope ps(PK_LEG_ANALYS, stream);
-            e = launch_sp_analys(a, p.L, p.M, p.ptab.jt(), p.ptab.analys_ct, stream);
+            e = launch_sp_analys(a, p.L, p.M, p.ptab.jt(), p.ptab.act(), stream);
         }
         if (e) return hip_error(e, "batch stored-P launch");
     }

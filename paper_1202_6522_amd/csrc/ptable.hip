@@ -380,15 +380,16 @@ __global__ void __launch_bounds__(64 * kSpWaves, 2) k_sp_analys(PtabArgs a)
             tq[q][t] = a.tab + blk * 256 + ptab_in_block(lane & 15, kk);  // + 256 pt + 16 (step % 4)
         }
     // the coefficients this thread puts in LDS, folded and weighted: pair
-    // 16 pt + lp of one field (8 CT fields: with one column tile half of the
-    // workgroup)
+    // 16 pt + lp of field lf (8 CT fields: with an odd CT half of the workgroup
+    // has one less)
     const int lp = tid & 15, lf = tid >> 4;
-    const bool loads = lf < 8 * CT;
-    const double2* fp;
-    {
-        const int f = blockIdx.y * CT * 8 + lf;
-        const int fc = f < a.nfields && loads ? f : 0;
-        fp = (const double2*)(a.in + (a.f_off ? a.f_off[fc] : (long)fc * 2 * P.f_size));
+    constexpr int NL = (CT + 1) / 2;  // fields per thread, 16 apart
+    const double2* fp[NL];
+#pragma unroll
+    for (int i = 0; i < NL; i++) {
+        const int f = blockIdx.y * CT * 8 + lf + 16 * i;
+        const int fc = f < a.nfields && lf + 16 * i < 8 * CT ? f : 0;
+        fp[i] = (const double2*)(a.in + (a.f_off ? a.f_off[fc] : (long)fc * 2 * P.f_size));
     }
 
     d4 acc[2][JT][CT];
@@ -417,23 +418,29 @@ __global__ void __launch_bounds__(64 * kSpWaves, 2) k_sp_analys(PtabArgs a)
         // (the loads stay ahead of the matrix instructions that follow)
         __builtin_amdgcn_sched_barrier(0);
     };
-    double2 vn, vs;
+    double2 vn[NL], vs[NL];
     double wv;
     auto load_f = [&](int pt) {
         const int pc = min(pt * 16 + lp, npair - 1);
         wv = P.wq[pc];
-        vn = fp[f_index(P.f_ts, m, pc)];
-        vs = fp[f_index(P.f_ts, m, nlat - 1 - pc)];
+#pragma unroll
+        for (int i = 0; i < NL; i++) {
+            vn[i] = fp[i][f_index(P.f_ts, m, pc)];
+            vs[i] = fp[i][f_index(P.f_ts, m, nlat - 1 - pc)];
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     auto put_f = [&](int pt) {
         const int pair = pt * 16 + lp;
         const bool middle = (nlat & 1) && pair == npair - 1;
         const double wt = pair >= npair ? 0.0 : (a.adjoint ? (middle ? 0.5 : 1.0) : wv);
-        if (loads) {
-            const int o = lp * kBRow + 2 * (lf & 7);
-            *(double2*)&bt[pt & 1][0][lf >> 3][o] = make_double2(wt * (vn.x + vs.x), wt * (vn.y + vs.y));
-            *(double2*)&bt[pt & 1][1][lf >> 3][o] = make_double2(wt * (vn.x - vs.x), wt * (vn.y - vs.y));
+        const int o = lp * kBRow + 2 * (lf & 7);
+#pragma unroll
+        for (int i = 0; i < NL; i++) {
+            if (lf + 16 * i >= 8 * CT) continue;
+            const int c = (lf >> 3) + 2 * i;
+            *(double2*)&bt[pt & 1][0][c][o] = make_double2(wt * (vn[i].x + vs[i].x), wt * (vn[i].y + vs[i].y));
+            *(double2*)&bt[pt & 1][1][c][o] = make_double2(wt * (vn[i].x - vs[i].x), wt * (vn[i].y - vs[i].y));
         }
     };
     auto run = [&](const Ops& o, int pt, int hf) {
@@ -524,24 +531,38 @@ static int launch_sp_analys_t(const PtabArgs& a, int L, int M, void* stream)
     return (int)hipGetLastError();
 }
 
-// A call of at most 8 fields fills one column tile: a second would only
-// add columns that are never stored.
+// Column tiles of a launch, and pair tiles (block rows) per wave.  ct > 0: as
+// set; a call of at most 8 fields fills one column tile, a second would only
+// add columns that are never stored.  ct = 0: one pair tile, and column tiles
+// for all fields up to 32, then as even as can be, so that the table is read as
+// few times as can be (24 fields at lmax 511, synthesis and analysis in us:
+// three column tiles 90.4 and 108.8, two and two 133.9 and 148.1).
+static int column_tiles(int nfields, int ct)
+{
+    const int all = (nfields + 7) / 8;
+    if (ct > 0) return all == 1 ? 1 : ct;
+    const int groups = (all + 3) / 4;
+    return (all + groups - 1) / groups;
+}
+
 int launch_sp_synth(const PtabArgs& a, int M, int rt, int ct, void* stream)
 {
-    if (a.nfields <= 8) ct = 1;
+    ct = column_tiles(a.nfields, ct);
 #define SHTN_SP(RV, CV) \
     if (rt == RV && ct == CV) return launch_sp_synth_t<RV, CV>(a, M, stream);
     SHTN_SP(1, 1) SHTN_SP(2, 1) SHTN_SP(4, 1) SHTN_SP(1, 2) SHTN_SP(2, 2) SHTN_SP(4, 2)
+    SHTN_SP(1, 3) SHTN_SP(1, 4)
 #undef SHTN_SP
     return (int)hipErrorInvalidValue;
 }
 
 int launch_sp_analys(const PtabArgs& a, int L, int M, int jt, int ct, void* stream)
 {
-    if (a.nfields <= 8) ct = 1;
+    ct = column_tiles(a.nfields, ct);
 #define SHTN_SP(JV, CV) \
     if (jt == JV && ct == CV) return launch_sp_analys_t<JV, CV>(a, L, M, stream);
     SHTN_SP(1, 1) SHTN_SP(2, 1) SHTN_SP(4, 1) SHTN_SP(1, 2) SHTN_SP(2, 2) SHTN_SP(4, 2)
+    SHTN_SP(1, 3) SHTN_SP(1, 4)
 #undef SHTN_SP
     return (int)hipErrorInvalidValue;
 }

@@ -176,6 +176,9 @@ struct PTable {
     bool auto_tiles = true;
     int rt() const { return auto_tiles ? 1 : synth_rt; }
     int jt() const { return auto_tiles ? 1 : analys_jt; }
+    // column tiles: 0 = by the number of fields (ptable.hip)
+    int sct() const { return auto_tiles ? 0 : synth_ct; }
+    int act() const { return auto_tiles ? 0 : analys_ct; }
 };
 
 struct Plan {
