@@ -232,6 +232,12 @@ int f_to_leg(const Plan& p, const double* F, double* Q, int nfields, int adjoint
     {
         ProfScope ps(PK_LEG_ANALYS, stream);
         l.top = top;
+        // half pieces when the plan has them and the call has few waves
+        auto few_waves = [&](long per_unit) {
+            if (p.short_units.empty() || l.nunits * per_unit > kShortUnits) return;
+            l.units = dev_table_int(p, TB_SHORT_UNITS);
+            l.nunits = (int)(p.short_units.size() / kUnitInts);
+        };
         if (const int mf = top ? mf_vec_fields(p.npair, nfields)
                                : (p.tiling.auto_fw ? mf_fields(p.npair, p.nlm, nfields) : 0)) {
             // the longest pieces that still give two waves for each of the
@@ -241,8 +247,10 @@ int f_to_leg(const Plan& p, const double* F, double* Q, int nfields, int adjoint
             while (k > 0 && (long)(p.mf_units[k].size() / kUnitInts) * groups * mf_waves(p.npair, mf) < 4096) k--;
             if (k > 0) l.units = dev_table_int(p, TB_MF_UNITS + k - 1);
             l.nunits = (int)(p.mf_units[k].size() / kUnitInts);
+            if (k == 0) few_waves(groups * mf_waves(p.npair, mf));
             e = launch_legendre_analys_mf(l, p.npair, mf, stream);
         } else {
+            if (p.tiling.auto_fw) few_waves((long)l.grid_y * l.waves);
             e = launch_legendre_analys(l, stream);
         }
     }

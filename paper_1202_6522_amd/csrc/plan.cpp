@@ -512,14 +512,20 @@ int rebuild_units(Plan& p, std::string& err)
     }
     if (S % kSegLen) { err = "split must be a multiple of 32"; return -1; }
     p.split_used = S;
+    // Small plans also get a list of half pieces, for calls that leave SIMDs
+    // idle (kShortUnits).
+    long whole = 0;
+    for (int m = 0; m <= M; m++) whole += (L - m + S) / S;
+    const bool halves = t.split <= 0 && S == 2 * kSegLen && whole <= kShortUnits;
+    const int rs = halves ? S / 2 : S;  // restart steps: rs, 2 rs, ...
     struct AU { int m, j0, j1, js, jw, rst; long cost; };
-    // restart slots: order by order, each order's restart steps S, 2 S, ...
+    // restart slots: order by order, each order's restart steps
     std::vector<std::vector<int>> rj(M + 1);
     std::vector<int> rbase(M + 1, 0);
     int nrst = 0;
     for (int m = 0; m <= M; m++) {
         rbase[m] = nrst;
-        for (int j0 = S; j0 < L - m + 1; j0 += S) rj[m].push_back(j0);
+        for (int j0 = rs; j0 < L - m + 1; j0 += rs) rj[m].push_back(j0);
         nrst += (int)rj[m].size();
     }
     auto make_piece = [&](int m, int j0, int j1) {
@@ -539,9 +545,9 @@ int rebuild_units(Plan& p, std::string& err)
             js = j1;  // nothing starts: the piece only writes zeros
             jw = -1;
         }
-        return AU{m, j0, j1, js, jw, j0 > 0 ? rbase[m] + j0 / S - 1 : -1, js < j1 ? analys_unit_cost(p, m, js, j1) : 0};
+        return AU{m, j0, j1, js, jw, j0 > 0 ? rbase[m] + j0 / rs - 1 : -1, js < j1 ? analys_unit_cost(p, m, js, j1) : 0};
     };
-    // the unit list for pieces of `len` degrees (a multiple of S)
+    // the unit list for pieces of `len` degrees (a multiple of rs)
     auto analys_list = [&](int len, std::vector<int>& units) {
         std::vector<std::vector<AU>> pieces(M + 1);
         std::vector<long> mcost(M + 1, 0);
@@ -582,6 +588,8 @@ int rebuild_units(Plan& p, std::string& err)
         }
     };
     analys_list(S, p.analys_units);
+    p.short_units.clear();
+    if (halves) analys_list(rs, p.short_units);
     // longer pieces for calls of many fields (analys_mf.hip)
     for (int k = 0; k < kMfLists; k++) analys_list(S << k, p.mf_units[k]);
     p.rst_y.assign((size_t)nrst * np * 2, 0.0);
@@ -663,6 +671,7 @@ void build_image(Plan& p)
     place(TB_ANALYS_UNITS, p.analys_units);
     place(TB_CK_MASK, p.ck_mask);
     for (int k = 1; k < kMfLists; k++) place(TB_MF_UNITS + k - 1, p.mf_units[k]);
+    place(TB_SHORT_UNITS, p.short_units);
     p.image.resize(off, 0);
 }
 

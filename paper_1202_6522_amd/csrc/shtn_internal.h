@@ -100,12 +100,19 @@ enum DevTable {
     TB_ANALYS_UNITS,
     TB_CK_MASK,
     TB_MF_UNITS,  // kMfLists - 1 tables (list 0 is TB_ANALYS_UNITS)
-    TB_COUNT = TB_MF_UNITS + 2
+    TB_SHORT_UNITS = TB_MF_UNITS + 2,
+    TB_COUNT
 };
 // Unit lists of the several-field analysis: pieces of 1, 2 and 4 times the
 // plan's split.
 constexpr int kMfLists = 3;
-static_assert(TB_COUNT == TB_MF_UNITS + kMfLists - 1, "one table per further list");
+static_assert(TB_SHORT_UNITS == TB_MF_UNITS + kMfLists - 1, "one table per further list");
+// Waves of an analysis with pieces of 64 degrees up to which pieces of 32 are
+// the faster: there are SIMDs to spare, and a wave's time is its steps
+// (one field, us: lmax 127 8.1 and 7.2, 255 9.9 and 8.0, 400, of 1470 waves, 13.0
+// and 11.8; 450, of 1860, 13.5 and 14.0; two fields at lmax 340, of 2160, 13.9 and
+// 14.9).
+constexpr long kShortUnits = 1600;
 
 // Lane-start summaries per block of 64 latitude pairs (the pair slot of a
 // wave lane: pairs [64 b, 64 b + 64) form block b).  blk_first[m][b]: the
@@ -200,6 +207,7 @@ struct Plan {
     std::vector<double> tw, rtw;
     std::vector<int> synth_units, analys_units;
     std::vector<int> mf_units[kMfLists];
+    std::vector<int> short_units;             // half pieces (see kShortUnits), or empty
     std::vector<int> first_pair;              // per m: first latitude pair kept by the polar cut
     double min_own_state = 0.0;               // see min_start_state
     std::vector<int> blk_first;               // (M+1) x nblk, see TB_BLK_FIRST
