@@ -303,6 +303,11 @@ int to_grid(shtn_plan_t plan, const double* Q, double* grid, int nfields, void* 
     int rc = check_call(plan, Q, Data::spec, grid, Data::grid, nfields, work);
     if (rc) return rc;
     const Plan& p = *plan->p;
+    if (p.tiling.auto_fw && !stored_synth(p.algo) && small_fits(p.M, p.nlat, p.K, p.nlm)) {
+        ProfScope ps(PK_LEG_SYNTH, stream);
+        const int e = launch_small_synth(fft_launch(p, nullptr, grid, nfields, 1.0), p.M, p.nlat, p.nlm, Q, adjoint, stream);
+        return e ? hip_fail(e, "small synthesis launch") : SHTN_OK;
+    }
     double* F = (double*)work;
     if ((rc = leg_to_f(p, Q, F, nfields, adjoint, stream))) return rc;
     return f_to_grid(p, F, grid, nfields, stream);
@@ -316,6 +321,12 @@ int to_spec(shtn_plan_t plan, const double* grid, double* Q, int nfields, void* 
     if (rc) return rc;
     const Plan& p = *plan->p;
     if ((rc = check_analys_stage(p))) return rc;
+    if (p.tiling.auto_fw && !stored_analys(p.algo) && small_fits(p.M, p.nlat, p.K, p.nlm)) {
+        ProfScope ps(PK_LEG_ANALYS, stream);
+        const FftLaunch l = fft_launch(p, grid, nullptr, nfields, adjoint ? 1.0 : 2.0 * 3.14159265358979323846 / p.nphi);
+        const int e = launch_small_analys(l, p.M, p.nlat, p.nlm, Q, adjoint, stream);
+        return e ? hip_fail(e, "small analysis launch") : SHTN_OK;
+    }
     double* F = (double*)work;
     if ((rc = grid_to_f(p, grid, F, nfields, adjoint ? 1.0 : 2.0 * 3.14159265358979323846 / p.nphi, stream)))
         return rc;

@@ -56,6 +56,9 @@ __host__ __device__ constexpr int fft_min_waves(int P, int lgk)
 // rows of fewer than 8 points), from a copy in LDS.
 __host__ __device__ constexpr bool fft_global_tw(int lgk) { return lgk >= 10; }
 
+// Threads of the largest workgroup of the small synthesis.
+constexpr int kSmallThreads = 512;
+
 // Twiddle tables are read through global-address-space pointers (the plan
 // descriptor holds them as generic pointers, which would compile to flat
 // loads).
@@ -567,17 +570,197 @@ __device__ __forceinline__ void move_f(double2* buf, const double* Fin, double* 
         break;                                 \
     }
 
+// ---------------------------------------------------------------------------
+// Small transforms: the Legendre stage and the longitude stage of a field in
+// one workgroup (k_small_synth, k_small_analys).  At these sizes a call is
+// latency: two launches, each with its own way from the plan to the data.
+// One field at lmax 31, synthesis and analysis: 8.0 and 8.0 us a call, of them
+// 5.8 and 7.2 on the GPU, against 10.5 and 10.4, 6.1 and 7.2; 512 fields 8.7 and
+// 10.5 on the GPU against 15.5 and 26.1.  Beyond one lane per (order, pair) of
+// the workgroup the GPU's time is longer than that of two launches (lmax 36,
+// synthesis: 8.7 against 7.5).
+// ---------------------------------------------------------------------------
+struct SmallArgs {
+    const double* q;   // synthesis: spectra
+    double* qout;      // analysis: spectra
+    int adjoint;
+};
+
+// F of every (order, latitude pair) of the plan, one per lane, into the points
+// of the rows in LDS.  The steps are those of the synthesis kernel
+// (legendre.hip), so the results are the same bits: coefficients times gamma,
+// the two-term recurrence from the lane's start on, even and odd degrees summed
+// apart, the segment shifts every kSegLen degrees.  qg, be: LDS for nlm
+// coefficients and nlm + kInject recurrence factors.
+__device__ __forceinline__ void small_legendre(double2* buf, double2* qg, double* be, const SmallArgs& sa,
+                                               const DevPlan& D, long field, int lgK, int nt)
+{
+    const int L = D.L, M = D.M, nlat = D.nlat, npair = D.npair, nlm = (int)D.nlm;
+    const int K = 1 << lgK, rs = row_shift(lgK);
+    {
+        const double2* q = (const double2*)sa.q + field * nlm;
+        for (int i = threadIdx.x; i < nlm + kInject; i += nt) {
+            const double b = D.beta[i];  // (the table is padded)
+            be[i] = b;
+            if (i < nlm) {
+                const double g = D.gamma[i];
+                const double2 v = q[i];
+                qg[i] = make_double2(g * v.x, g * v.y);
+            }
+        }
+    }
+    for (int idx = threadIdx.x; idx < nlat << lgK; idx += nt)
+        if ((idx & (K - 1)) > M) buf[at(idx, rs)] = make_double2(0.0, 0.0);
+    const int lanes = (M + 1) * npair;
+    __syncthreads();
+    for (int e = threadIdx.x; e < lanes; e += nt) {
+        const int m = e / npair, pair = e - m * npair;
+        const int nj = L - m + 1, base = m * (2 * L + 1 - m) / 2 + m;
+        const double x = D.xp[pair];
+        const int jst = D.inj_j[e];  // a multiple of kInject, nj or more if the lane never starts
+        const double2 y = *(const double2*)(D.inj_y + 2 * (size_t)e);
+        const int* segexp = D.segexp + D.segoff[m];
+        double ua = y.x, ub = y.y, er = 0.0, ei = 0.0, orr = 0.0, oi = 0.0;
+        for (int j = jst; j < nj; j += kInject) {
+            if (j > jst && (j & (kSegLen - 1)) == 0) {
+                const int sh = segexp[j / kSegLen];
+                ua = __builtin_amdgcn_ldexp(ua, sh);
+                ub = __builtin_amdgcn_ldexp(ub, sh);
+            }
+            double2 c[kInject];
+            double b[kInject];
+#pragma unroll
+            for (int t = 0; t < kInject; t++) {
+                const double2 v = qg[min(base + j + t, nlm - 1)];
+                c[t] = j + t < nj ? v : make_double2(0.0, 0.0);
+                b[t] = be[base + j + t];
+            }
+#pragma unroll
+            for (int t = 0; t < kInject; t += 2) {
+                ua = fma(x, ub, b[t] * ua);
+                er = fma(c[t].x, ua, er);
+                ei = fma(c[t].y, ua, ei);
+                ub = fma(x, ua, b[t + 1] * ub);
+                orr = fma(c[t + 1].x, ub, orr);
+                oi = fma(c[t + 1].y, ub, oi);
+            }
+        }
+        // mirror fold; Im F_0 is not used
+        const double cm = sa.adjoint ? (2.0 * 3.14159265358979323846 / D.nphi) * (m == 0 ? 1.0 : 0.5) : 1.0;
+        const double sc = sa.adjoint ? cm * D.wfull[pair] : 1.0;
+        const int is = nlat - 1 - pair;
+        buf[at((pair << lgK) + m, rs)] = make_double2(sc * (er + orr), m == 0 ? 0.0 : sc * (ei + oi));
+        if (is != pair) buf[at((is << lgK) + m, rs)] = make_double2(sc * (er - orr), m == 0 ? 0.0 : sc * (ei - oi));
+    }
+}
+
+// v of lane l ^ D, D = 2, 4, 8 (rows of 16 lanes: DPP quad_perm [2,3,0,1],
+// row_half_mirror and quad_perm [3,2,1,0], row_ror:8) or 16.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+template <int D>
+__device__ __forceinline__ double xor_lane(double v)
+{
+    if constexpr (D == 2)
+        return dpp_move<0x4E>(v);
+    else if constexpr (D == 4)
+        return dpp_move<0x1B>(dpp_move<0x141>(v));
+    else if constexpr (D == 8)
+        return dpp_move<0x128>(v);
+    else
+        return __shfl_xor(v, D);
+}
+
+// Spectra of the field whose F is in the points of the rows in LDS: G = 16 or 32
+// lanes per order, one per latitude pair.  Steps and sums are those of the
+// analysis kernel (legendre.hip: lane pairs first, then its columns in its
+// order, which here are exchanges between lanes), so the results are the same
+// bits.  be, ga: LDS for nlm + kInject recurrence factors and nlm gammas, filled
+// before.
+template <int G>
+__device__ __forceinline__ void small_analysis(const double2* buf, const double* be, const double* ga,
+                                               const SmallArgs& sa, const DevPlan& D, long field, int lgK, int nt)
+{
+    const int L = D.L, M = D.M, nlat = D.nlat, npair = D.npair, nlm = (int)D.nlm;
+    const int rs = row_shift(lgK);
+    const int pair = threadIdx.x & (G - 1);
+    const bool odd = pair & 1, act = pair < npair;
+    const int pc = act ? pair : 0;
+    const double x = act ? D.xp[pc] : 0.0;
+    const bool middle = (nlat & 1) && pair == npair - 1;
+    const double wt = !act ? 0.0 : (sa.adjoint ? (middle ? 0.5 : 1.0) : D.wq[pc]);
+    double* out = sa.qout + field * 2 * nlm;
+    for (int m = threadIdx.x / G; m <= M; m += nt / G) {
+        const int nj = L - m + 1, base = m * (2 * L + 1 - m) / 2 + m;
+        const size_t e = (size_t)m * npair + pc;
+        const int jst = act ? D.inj_j[e] : nj;
+        const double2 y = *(const double2*)(D.inj_y + 2 * e);
+        const int* segexp = D.segexp + D.segoff[m];
+        const double2 vn = buf[at((pc << lgK) + m, rs)], vs = buf[at(((nlat - 1 - pc) << lgK) + m, rs)];
+        const double er = wt * (vn.x + vs.x), ei = wt * (vn.y + vs.y);
+        const double orr = wt * (vn.x - vs.x), oi = wt * (vn.y - vs.y);
+        // the part this lane keeps and the one it hands to its neighbour
+        const double ek = odd ? ei : er, es = odd ? er : ei, ok = odd ? oi : orr, os = odd ? orr : oi;
+        const double cm = (m == 0 || !sa.adjoint) ? 1.0 : 2.0;
+        double ua = 0.0, ub = 0.0;
+        for (int j = 0; j < nj; j += kInject) {
+            if (j > 0 && (j & (kSegLen - 1)) == 0) {
+                const int sh = segexp[j / kSegLen];
+                ua = __builtin_amdgcn_ldexp(ua, sh);
+                ub = __builtin_amdgcn_ldexp(ub, sh);
+            }
+            if (j == jst) {
+                ua = y.x;
+                ub = y.y;
+            }
+            double v[kInject];
+#pragma unroll
+            for (int t = 0; t < kInject; t += 2) {
+                ua = fma(x, ub, be[base + j + t] * ua);
+                ub = fma(x, ua, be[base + j + t + 1] * ub);
+                // (fma with 0: rounded products, as the analysis kernel's first)
+                v[t] = fma(ek, ua, 0.0) + swap_pair(fma(es, ua, 0.0));
+                v[t + 1] = fma(ok, ub, 0.0) + swap_pair(fma(os, ub, 0.0));
+            }
+            // the sum of the columns: lane 2 t + comp keeps that of step t
+            double sum = 0.0;
+#pragma unroll
+            for (int t = 0; t < kInject; t++) {
+                double c = v[t];
+                if constexpr (G == 32) c += xor_lane<16>(c);
+                c += xor_lane<4>(c);
+                c += xor_lane<8>(c);
+                c += xor_lane<2>(c);
+                sum = (pair >> 1) == t ? c : sum;
+            }
+            const int jo = j + (pair >> 1);
+            if (pair < 2 * kInject && jo < nj) {
+                const int comp = pair & 1;
+                out[2 * (base + jo) + comp] = m == 0 && comp == 1 ? 0.0 : cm * ga[base + jo] * sum;
+            }
+        }
+    }
+}
+
 // Fourier synthesis of rows: f_ik = Re F_0 + 2 Re sum_{m=1}^{M} F_m e^{2 pi i m k / N}.
 // LGK > 0: rows of K = 2^LGK points, so the passes and all index arithmetic
 // are fixed at compile time; LGK = 0: any K; LGK < 0 (the kernel alone): by
 // each block's K.
-template <int P, int LGK>
-__device__ __forceinline__ void c2r_rows(const FftArgs& a, const DevPlan& D, const RowBlock& rb)
+// SMALL: the block is a whole field, whose F comes from small_legendre.
+template <int P, int LGK, bool SMALL = false>
+__device__ __forceinline__ void c2r_rows(const FftArgs& a, const DevPlan& D, const RowBlock& rb,
+                                         const SmallArgs* sa = nullptr)
 {
     extern __shared__ double2 lds[];  // points (P per thread), then the twiddle table
     double2* buf = lds;
     constexpr bool GT = fft_global_tw(LGK);
-    double2* twl = lds + lds_points(blockDim.x * P);  // unused with GT
+    double2* twl = lds + lds_points(SMALL ? rb.nrows << LGK : blockDim.x * P);  // unused with GT
     const int K = LGK > 0 ? 1 << LGK : D.K, M = D.M, nlat = D.nlat, nphi = D.nphi;
     const int lgK = LGK > 0 ? LGK : __builtin_ctz(K), rs = row_shift(lgK);
     const gdp tw = (gdp)D.tw;
@@ -586,7 +769,7 @@ __device__ __forceinline__ void c2r_rows(const FftArgs& a, const DevPlan& D, con
     double* g = (in_grid2(a, rb.field) ? a.grid2 : a.out) + grid_off(a, rb.field, nlat, nphi);
     const int npts = rb.nrows << lgK;
     // the block's threads: whole waves, P points each; the others end here
-    const int nt = (((npts + P - 1) / P) + 63) & ~63;
+    const int nt = SMALL ? (int)blockDim.x : (((npts + P - 1) / P) + 63) & ~63;
     if ((int)threadIdx.x >= nt) return;
 
     // Z_m = (Y_m + conj Y_{K-m}) + i w^m (Y_m - conj Y_{K-m}), w = e^{i pi/K},
@@ -602,7 +785,7 @@ __device__ __forceinline__ void c2r_rows(const FftArgs& a, const DevPlan& D, con
     // read one 64-byte run of a tile), forms Z and runs that pass in
     // registers: Y never goes through LDS.  A block of one row (K = 4096)
     // would read every F value twice in 16-byte pieces; it goes through LDS.
-    if (fused && rb.nrows >= 2 && (rb.nrows & (rb.nrows - 1)) == 0 && rb.nrows <= kFTile &&
+    if (!SMALL && fused && rb.nrows >= 2 && (rb.nrows & (rb.nrows - 1)) == 0 && rb.nrows <= kFTile &&
         (rb.row0 & (rb.nrows - 1)) == 0) {
         const int lgr = __builtin_ctz(rb.nrows);
         const int lgKR = lgK - LGP;
@@ -661,9 +844,14 @@ __device__ __forceinline__ void c2r_rows(const FftArgs& a, const DevPlan& D, con
         for (int e = 0; e < P; e++) rw[e] = ld2(rtw, (threadIdx.x + e * nt) & (K - 1));
     }
     // Y_m (Y_0 = Re F_0, Y_m = F_m for 1 <= m <= M, 0 above) row by row
-    for (int idx = threadIdx.x; idx < npts; idx += nt)
-        if ((idx & (K - 1)) > M) buf[at(idx, rs)] = make_double2(0.0, 0.0);
-    move_f<P, true>(buf, F, nullptr, D.f_ts, M, lgK, rb.row0, rb.nrows, nt);
+    if constexpr (SMALL) {
+        double2* qg = twl + tw_slots(K);
+        small_legendre(buf, qg, (double*)(qg + D.nlm), *sa, D, rb.field, lgK, nt);
+    } else {
+        for (int idx = threadIdx.x; idx < npts; idx += nt)
+            if ((idx & (K - 1)) > M) buf[at(idx, rs)] = make_double2(0.0, 0.0);
+        move_f<P, true>(buf, F, nullptr, D.f_ts, M, lgK, rb.row0, rb.nrows, nt);
+    }
     if (!GT) stage_twiddles(twl, tw, K, nt);
     __syncthreads();
     bool stored;
@@ -715,15 +903,25 @@ __global__ void __launch_bounds__(fft_max_threads(P, LGK), fft_min_waves(P, LGK)
         SHTN_BY_ROW_LENGTH(c2r_rows)
 }
 
+// One workgroup per field.
+template <int LGK>
+__global__ void __launch_bounds__(kSmallThreads, 2) k_small_synth(FftArgs a, SmallArgs sa)
+{
+    const DevPlan& D = *a.plans;
+    c2r_rows<8, LGK, true>(a, D, RowBlock{(int)blockIdx.x, 0, 0, D.nlat}, &sa);
+}
+
 // Fourier analysis of rows: F_m(theta_i) = scale * sum_k f_ik e^{-2 pi i m k / N}, m <= M
 // (LGK as for k_c2r).
-template <int P, int LGK>
-__device__ __forceinline__ void r2c_rows(const FftArgs& a, const DevPlan& D, const RowBlock& rb)
+// SMALL: the block is a whole field, whose F goes to small_analysis.
+template <int P, int LGK, bool SMALL = false>
+__device__ __forceinline__ void r2c_rows(const FftArgs& a, const DevPlan& D, const RowBlock& rb,
+                                         const SmallArgs* sa = nullptr)
 {
     extern __shared__ double2 lds[];  // points (P per thread), then the twiddle table
     double2* buf = lds;
     constexpr bool GT = fft_global_tw(LGK);
-    double2* twl = lds + lds_points(blockDim.x * P);  // unused with GT
+    double2* twl = lds + lds_points(SMALL ? rb.nrows << LGK : blockDim.x * P);  // unused with GT
     const int K = LGK > 0 ? 1 << LGK : D.K, M = D.M, nlat = D.nlat, nphi = D.nphi;
     const int lgK = LGK > 0 ? LGK : __builtin_ctz(K), rs = row_shift(lgK);
     const gdp tw = (gdp)D.tw;
@@ -732,7 +930,7 @@ __device__ __forceinline__ void r2c_rows(const FftArgs& a, const DevPlan& D, con
     double* F = a.out + (a.f_off ? a.f_off[rb.field] : (long)rb.field * 2 * D.f_size);
     const int npts = rb.nrows << lgK;
     // the block's threads: whole waves, P points each; the others end here
-    const int nt = (((npts + P - 1) / P) + 63) & ~63;
+    const int nt = SMALL ? (int)blockDim.x : (((npts + P - 1) / P) + 63) & ~63;
     if ((int)threadIdx.x >= nt) return;
     // Straight-line loads from valid addresses, then LDS writes without
     // branches (idx < P blockDim stays inside the point buffer; slots past
@@ -764,7 +962,7 @@ __device__ __forceinline__ void r2c_rows(const FftArgs& a, const DevPlan& D, con
     // (the usual case), each thread computes the outputs X_m it stores,
     // straight from Z in LDS (entry e: order e >> lg, row e & (nrows - 1));
     // otherwise a post-pass writes X over the buffer first.
-    const bool direct = (rb.nrows & (rb.nrows - 1)) == 0 && rb.nrows <= kFTile && (rb.row0 & (rb.nrows - 1)) == 0;
+    const bool direct = !SMALL && (rb.nrows & (rb.nrows - 1)) == 0 && rb.nrows <= kFTile && (rb.row0 & (rb.nrows - 1)) == 0;
     const int lgr = __builtin_ctz(rb.nrows);
     const int nout = rb.nrows * (M + 1);
     // w^m of this thread's outputs for the post-pass.  Rows of 64 or more
@@ -794,6 +992,14 @@ __device__ __forceinline__ void r2c_rows(const FftArgs& a, const DevPlan& D, con
         return factor(order_of(e));
     };
     if (!GT) stage_twiddles(twl, tw, K, nt);
+    double* be = (double*)(twl + tw_slots(K));
+    double* ga = be + D.nlm + kInject;
+    if constexpr (SMALL) {
+        for (int i = threadIdx.x; i < (int)D.nlm + kInject; i += nt) {
+            be[i] = D.beta[i];  // (the table is padded)
+            if (i < (int)D.nlm) ga[i] = D.gamma[i];
+        }
+    }
     if (first_in_regs) {
         // the first pass (Ns = 1, no twiddles): DFT of the loaded points,
         // outputs to slots (jj << lg P) + q of the row
@@ -851,14 +1057,22 @@ __device__ __forceinline__ void r2c_rows(const FftArgs& a, const DevPlan& D, con
     double2 x[P];
 #pragma unroll
     for (int e = 0; e < P; e++) {
-        const int idx = threadIdx.x + e * nt;
+        const int idx = SMALL ? min((int)threadIdx.x + e * nt, npts - 1) : threadIdx.x + e * nt;
         const int m = idx & (K - 1);
         x[e] = post(buf[at(idx, rs)], cconj(buf[at(idx - m + ((K - m) & (K - 1)), rs)]), rfac(e), m);
     }
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < P; e++) buf[at(threadIdx.x + e * nt, rs)] = x[e];
+    for (int e = 0; e < P; e++)
+        if (!SMALL || (int)threadIdx.x + e * nt < npts) buf[at(threadIdx.x + e * nt, rs)] = x[e];
     __syncthreads();
+    if constexpr (SMALL) {
+        if (D.npair <= 16)
+            small_analysis<16>(buf, be, ga, *sa, D, rb.field, lgK, nt);
+        else
+            small_analysis<32>(buf, be, ga, *sa, D, rb.field, lgK, nt);
+        return;
+    }
     move_f<P, false>(buf, nullptr, F, D.f_ts, M, lgK, rb.row0, rb.nrows, nt);
 }
 
@@ -872,6 +1086,13 @@ __global__ void __launch_bounds__(fft_max_threads(P, LGK), fft_min_waves(P, LGK)
         r2c_rows<P, LGK>(a, D, rb);
     else
         SHTN_BY_ROW_LENGTH(r2c_rows)
+}
+
+template <int LGK>
+__global__ void __launch_bounds__(kSmallThreads, 2) k_small_analys(FftArgs a, SmallArgs sa)
+{
+    const DevPlan& D = *a.plans;
+    r2c_rows<8, LGK, true>(a, D, RowBlock{(int)blockIdx.x, 0, 0, D.nlat}, &sa);
 }
 
 static FftArgs fft_args(const FftLaunch& l)
@@ -970,6 +1191,51 @@ static int launch_fft(const FftLaunch& l, void* stream)
 }
 
 int launch_c2r(const FftLaunch& l, void* stream) { return launch_fft<true>(l, stream); }
+
+// Points, twiddles and either coefficients and recurrence factors (synthesis)
+// or recurrence factors and gammas.
+static size_t small_lds_bytes(int points, int K, long nlm)
+{
+    return sizeof(double2) * ((size_t)lds_points(points) + 1 + tw_slots(K) + nlm) + sizeof(double) * (nlm + kInject);
+}
+
+// A lane per (order, pair), lane groups of at most 32 pairs, and LDS within the
+// default 64 KB.
+bool small_fits(int M, int nlat, int K, long nlm)
+{
+    return K >= 8 && nlat <= 64 && K <= 64 && nlat <= kFftPoints / K && nlm <= kFftPoints && small_lds_bytes(nlat * K, K, nlm) <= 65536 &&
+           (M + 1) * ((nlat + 1) / 2) <= kSmallThreads;
+}
+
+template <bool SYNTH>
+static int launch_small(const FftLaunch& l, int M, int nlat, long nlm, const SmallArgs& sa, void* stream)
+{
+    const int lanes = (M + 1) * ((nlat + 1) / 2), pts = nlat * l.K;
+    const int nt = std::min(kSmallThreads, (std::max(lanes, (pts + 7) / 8) + 63) / 64 * 64);
+    const size_t lds = small_lds_bytes(pts, l.K, nlm);
+#define SHTN_SMALL(LGK)                                                                                            \
+    if (l.K == 1 << LGK) {                                                                                         \
+        if (SYNTH)                                                                                                 \
+            hipLaunchKernelGGL((k_small_synth<LGK>), dim3(l.nfields), dim3(nt), lds, (hipStream_t)stream,          \
+                               fft_args(l), sa);                                                                   \
+        else                                                                                                       \
+            hipLaunchKernelGGL((k_small_analys<LGK>), dim3(l.nfields), dim3(nt), lds, (hipStream_t)stream,         \
+                               fft_args(l), sa);                                                                   \
+    }
+    SHTN_SMALL(3) SHTN_SMALL(4) SHTN_SMALL(5) SHTN_SMALL(6)
+#undef SHTN_SMALL
+    return (int)hipGetLastError();
+}
+
+int launch_small_synth(const FftLaunch& l, int M, int nlat, long nlm, const double* q, int adjoint, void* stream)
+{
+    return launch_small<true>(l, M, nlat, nlm, SmallArgs{q, nullptr, adjoint}, stream);
+}
+
+int launch_small_analys(const FftLaunch& l, int M, int nlat, long nlm, double* q, int adjoint, void* stream)
+{
+    return launch_small<false>(l, M, nlat, nlm, SmallArgs{nullptr, q, adjoint}, stream);
+}
 
 int launch_r2c(const FftLaunch& l, void* stream) { return launch_fft<false>(l, stream); }
 

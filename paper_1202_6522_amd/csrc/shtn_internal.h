@@ -431,6 +431,11 @@ int launch_c2r(const FftLaunch& a, void* stream);
 int fft_rows_cap(int K);     // rows of K complex points held by one FFT workgroup
 int fft_rows_auto(int K);    // rows per workgroup unless the caller sets them
 int launch_r2c(const FftLaunch& a, void* stream);
+// Both stages of a synthesis or analysis in one launch, for plans so small that
+// a field fits one workgroup (fft.hip); q: spectra.
+bool small_fits(int M, int nlat, int K, long nlm);
+int launch_small_analys(const FftLaunch& l, int M, int nlat, long nlm, double* q, int adjoint, void* stream);
+int launch_small_synth(const FftLaunch& l, int M, int nlat, long nlm, const double* q, int adjoint, void* stream);
 
 }  // namespace shtn
 
