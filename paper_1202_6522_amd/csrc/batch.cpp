@@ -93,6 +93,16 @@ struct shtn_batch_s {
 
 namespace {
 
+// A synthesis unit's set-up next to its degrees (one of 40 degrees takes about
+// twice as long as one of none).  Without it, one queue took nearly all the
+// short orders of a batch of a few long and many short ones.
+constexpr long kUnitSetup = 40;
+
+// Most units a queue may take of `total` units in orders of up to `blocks`
+// units.  An order always finds a queue with room: the shortest one holds at
+// most total / kXcds before the order is dealt.
+size_t queue_cap(size_t total, size_t blocks) { return (total + total / 8) / kXcds + blocks + 1; }
+
 size_t put_bytes(std::vector<unsigned char>& img, size_t off, const void* src, size_t bytes)
 {
     if (img.size() < off + bytes) img.resize(off + bytes);
@@ -136,7 +146,7 @@ void build_tables(shtn_batch_s& b, const BatchTiling& t)
 
     // ---- synthesis units ----
     // (the latitude blocks of one order and field group go to the XCD with the
-    // least work so far, largest first, and share its L2)
+    // least work so far among those with room, largest first, and share its L2)
     struct OrderUnits {
         long cost;
         std::vector<SynthUnit> u;
@@ -162,6 +172,7 @@ void build_tables(shtn_batch_s& b, const BatchTiling& t)
         }
     }
     const int sfw = b.synth_fw;
+    size_t total = 0, blocks = 0;
     for (size_t pi = 0; pi < b.plans.size(); pi++) {
         if (stored[pi]) continue;
         const Plan& p = *b.plans[pi];
@@ -182,9 +193,11 @@ void build_tables(shtn_batch_s& b, const BatchTiling& t)
                     } else {
                         x.u[U_ZERO] = 1;
                     }
-                    o.cost += x.cost;
+                    o.cost += kUnitSetup + x.cost;
                     o.u.push_back(x);
                 }
+                total += o.u.size();
+                blocks = std::max(blocks, o.u.size());
                 ou.push_back(std::move(o));
             }
         }
@@ -193,10 +206,11 @@ void build_tables(shtn_batch_s& b, const BatchTiling& t)
     {
         std::vector<SynthUnit> sq[kXcds];
         long load[kXcds] = {0};
+        const size_t cap = queue_cap(total, blocks);
         for (auto& o : ou) {
-            int x = 0;
-            for (int k = 1; k < kXcds; k++)
-                if (load[k] < load[x]) x = k;
+            int x = -1;
+            for (int k = 0; k < kXcds; k++)
+                if (sq[k].size() + o.u.size() <= cap && (x < 0 || load[k] < load[x])) x = k;
             load[x] += o.cost;
             sq[x].insert(sq[x].end(), o.u.begin(), o.u.end());
         }
@@ -287,6 +301,23 @@ void build_tables(shtn_batch_s& b, const BatchTiling& t)
     b.off_au = off; off = put_vec(b.image, off, b.analys_units);
     b.off_rb = off; off = put_vec(b.image, off, b.rowblocks);
     b.image.resize(off, 0);
+}
+
+// Largest image over all tilings and polar thresholds: the one with the most
+// units (a field and 64 latitude pairs per wave, nothing stored) and every
+// synthesis queue as long as it may get.  The other tables depend on neither.
+size_t image_bound(shtn_batch_s& b)
+{
+    build_tables(b, BatchTiling{});
+    size_t total = 0, blocks = 0;
+    for (int pi : b.slot_plan) {
+        const Plan& p = *b.plans[pi];
+        const size_t nblk = (p.npair + 63) / 64;
+        total += (p.M + 1) * nblk;
+        blocks = std::max(blocks, nblk);
+    }
+    return b.image.size() - (b.off_au - b.off_su) +
+           align256(kXcds * queue_cap(total, blocks) * kUnitInts * sizeof(int));
 }
 
 template <typename T>
@@ -473,10 +504,11 @@ int upload(shtn_batch_s& b, void* dev_buf, void* stream)
         } catch (const std::bad_alloc&) {
             return set_error(SHTN_ENOMEM, "out of host memory");
         }
-        if (b.image.size() > b.max_image)
-            return set_error(SHTN_ESTATE, "the batch's plans changed so that its tables no longer fit the buffer "
-                                          "sized by shtn_batch_device_bytes: create the batch again");
     }
+    // (the caller's buffer has shtn_batch_device_bytes)
+    if (b.image.size() > b.max_image)
+        return set_error(SHTN_ESTATE, "the batch's plans changed so that its tables no longer fit the buffer "
+                                      "sized by shtn_batch_device_bytes: create the batch again");
     // descriptors of the plans as uploaded (device pointers to their tables)
     for (size_t i = 0; i < b.plans.size(); i++) {
         const Plan& p = *b.plans[i];
@@ -660,16 +692,9 @@ shtn_batch_t shtn_batch(int nfields, const shtn_plan_t* plans)
         }
         so += 2 * (size_t)kTablePad;  // block loads may run past the last field
         b->work_total_bytes = align256((fo + so) * 8);
-        // the largest image over the tiling space (one field per wave, one
-        // order and one pair per lane, separate analysis classes)
-        BatchTiling worst;
-        build_tables(*b, worst);
-        b->max_image = b->image.size();
+        b->max_image = image_bound(*b);
         b->tiling.auto_fw = true;
         build_tables(*b, b->tiling);
-        // (the padding of the queues differs between tilings by less than an
-        // order's blocks per XCD)
-        b->max_image = std::max(b->max_image, b->image.size()) + kXcds * 64 * kUnitInts * sizeof(int);
         return b;
     } catch (const std::bad_alloc&) {
         set_error(SHTN_ENOMEM, "out of host memory");
