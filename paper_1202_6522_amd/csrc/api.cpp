@@ -96,6 +96,42 @@ int check_call(shtn_plan_t plan, const void* in, Data kin, const void* out, Data
     return check_disjoint(r);
 }
 
+// Rebuilds the unit lists, restart states and device image after a change of
+// the tiling or the lane starts; the plan is then to be uploaded again.  When
+// that fails, `restore` puts the settings back and the tables are built for
+// them (and if even that fails, the plan is left without: its upload is
+// refused).
+template <class F>
+int rebuild_tables(Plan& p, F restore)
+{
+    std::string err;
+    int rc = SHTN_EINVAL;
+    try {
+        if (!rebuild_units(p, err)) {
+            build_image(p);
+            p.uploaded = false;
+            p.dev = nullptr;
+            p.gen++;
+            return SHTN_OK;
+        }
+    } catch (const std::bad_alloc&) {
+        rc = SHTN_ENOMEM;
+        err = "out of host memory";
+    }
+    try {
+        std::string ignored;
+        restore();
+        rebuild_units(p, ignored);
+        build_image(p);
+    } catch (const std::bad_alloc&) {
+        p.image.clear();
+        p.uploaded = false;
+        p.dev = nullptr;
+        p.gen++;
+    }
+    return fail(rc, err);
+}
+
 // Which passes of an algorithm choice read the stored table.
 bool stored_synth(int algo) { return algo == SHTN_ALGO_STORED || algo == SHTN_ALGO_STORED_SYNTH; }
 bool stored_analys(int algo) { return algo == SHTN_ALGO_STORED || algo == SHTN_ALGO_STORED_ANALYS; }
@@ -401,6 +437,7 @@ int shtn_plan_upload(shtn_plan_t plan, void* dev_buf, void* stream)
     if (!dev_buf) return fail(SHTN_EINVAL, "null device buffer");
     if ((uintptr_t)dev_buf % 256) return fail(SHTN_EINVAL, "device buffer must be 256-byte aligned");
     Plan& p = *plan->p;
+    if (p.image.empty()) return fail(SHTN_ESTATE, "the plan's tables could not be rebuilt: create the plan again");
     char* base = (char*)dev_buf;
     DevPlan d{};
     auto at = [&](int tb) { return (const void*)(base + p.table_off[tb]); };
@@ -569,18 +606,7 @@ int shtn_plan_set_tiling(shtn_plan_t plan, int synth_lp, int analys_lp, int anal
     p.tiling.m_pairing = m_pairing;
     p.tiling.split = split;
     p.tiling.fft_rows = fft_rows;
-    std::string err;
-    if (rebuild_units(p, err)) {
-        p.tiling = old;
-        rebuild_units(p, err);
-        build_image(p);
-        return fail(SHTN_EINVAL, err);
-    }
-    build_image(p);
-    p.uploaded = false;
-    p.dev = nullptr;
-    p.gen++;
-    return SHTN_OK;
+    return rebuild_tables(p, [&] { p.tiling = old; });
 }
 
 int shtn_plan_set_polar(shtn_plan_t plan, int log2_threshold)
@@ -610,19 +636,12 @@ int shtn_plan_set_polar(shtn_plan_t plan, int log2_threshold)
         return fail(SHTN_EINVAL, "polar threshold too low for this plan: lane start states fall below the "
                                  "normal double range");
     }
-    std::string err;
-    if (rebuild_units(p, err)) {
+    const int rc = rebuild_tables(p, [&] {
         p.polar_log2 = old;
         lane_starts(p);
-        rebuild_units(p, err);
-        build_image(p);
-        return fail(SHTN_EINVAL, err);
-    }
-    build_image(p);
-    p.uploaded = false;
-    p.dev = nullptr;
+    });
+    if (rc) return rc;
     p.ptab.built = false;  // the table follows the lane starts
-    p.gen++;
     return SHTN_OK;
 }
 

@@ -512,6 +512,8 @@ int rebuild_units(Plan& p, std::string& err)
     }
     if (S % kSegLen) { err = "split must be a multiple of 32"; return -1; }
     p.split_used = S;
+    // (pieces longer than the longest order are the same as one of its length)
+    if (t.split > 0) S = std::min(S, (L + kSegLen) / kSegLen * kSegLen);
     // Small plans also get a list of half pieces, for calls that leave SIMDs
     // idle (kShortUnits).
     long whole = 0;
@@ -590,8 +592,13 @@ int rebuild_units(Plan& p, std::string& err)
     analys_list(S, p.analys_units);
     p.short_units.clear();
     if (halves) analys_list(rs, p.short_units);
-    // longer pieces for calls of many fields (analys_mf.hip)
-    for (int k = 0; k < kMfLists; k++) analys_list(S << k, p.mf_units[k]);
+    // longer pieces for calls of many fields (analys_mf.hip), which a set tiling
+    // does not take
+    p.mf_units[0] = p.analys_units;
+    for (int k = 1; k < kMfLists; k++) {
+        p.mf_units[k].clear();
+        if (t.auto_fw) analys_list(S << k, p.mf_units[k]);
+    }
     p.rst_y.assign((size_t)nrst * np * 2, 0.0);
     // restart states, orders split over host threads
     unsigned nth = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
