@@ -159,17 +159,20 @@ __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
                            : (unsigned)min((lane >> 1) & 1, nf - 1) * (unsigned)(P->f_size * 16) + 8 * (lane & 1);
         const unsigned ts16 = (unsigned)fts * 16;
         gcp xp = (gcp)P->xp, wq = (gcp)P->wq;
+        // (past the last pair the first one's values, with weight 0, as in the
+        // vector kernel: seen only when they are infinite or not a number)
+        auto pair_of = [&](int i) { return (unsigned)(i < npair ? i : 0); };
         auto lat_off = [&](int i) { return (unsigned)(i >> kFTileLg) * ts16 + (unsigned)(i & (kFTile - 1)) * 16; };
 #pragma unroll
         for (int p = 0; p < LP; p++) {
-            x[p] = ld1(xp, 8 * (unsigned)min(pb + p * 64 + lane, npair - 1));
+            x[p] = ld1(xp, 8 * pair_of(pb + p * 64 + lane));
 #pragma unroll
             for (int s = 0; s < 4; s++) {
                 // B rows: the pairs whose values sit in lanes 16 k + 4 b + s
-                const int pair = min(pb + p * 64 + (lane & 60) + s, npair - 1);
-                w[p][s] = ld1(wq, 8 * (unsigned)pair);
-                if constexpr (VEC) xs[p][s] = ld1(xp, 8 * (unsigned)pair);
-                const unsigned on = lat_off(pair), os = lat_off(nlat - 1 - pair);
+                const unsigned pair = pair_of(pb + p * 64 + (lane & 60) + s);
+                w[p][s] = ld1(wq, 8 * pair);
+                if constexpr (VEC) xs[p][s] = ld1(xp, 8 * pair);
+                const unsigned on = lat_off((int)pair), os = lat_off(nlat - 1 - (int)pair);
 #pragma unroll
                 for (int v = 0; v < NV; v++) {
                     if constexpr (CG > 1) {
@@ -188,7 +191,7 @@ __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
         if (from_rst) {
             gcp ry = (gcp)(P->rst_y + 2 * ((size_t)rst * npair));
 #pragma unroll
-            for (int p = 0; p < LP; p++) r[p] = ld2(ry, 16 * (unsigned)min(pb + p * 64 + lane, npair - 1));
+            for (int p = 0; p < LP; p++) r[p] = ld2(ry, 16 * pair_of(pb + p * 64 + lane));
         } else {
 #pragma unroll
             for (int p = 0; p < LP; p++) r[p] = make_double2(0.0, 0.0);

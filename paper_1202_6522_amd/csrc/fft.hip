@@ -589,8 +589,9 @@ struct SmallArgs {
 // F of every (order, latitude pair) of the plan, one per lane, into the points
 // of the rows in LDS.  The steps are those of the synthesis kernel
 // (legendre.hip), so the results are the same bits: coefficients times gamma,
-// the two-term recurrence from the lane's start on, even and odd degrees summed
-// apart, the segment shifts every kSegLen degrees.  qg, be: LDS for nlm
+// the two-term recurrence from the order's first degree on (every lane starts
+// there), even and odd degrees summed apart, the segment shifts every kSegLen
+// degrees.  qg, be: LDS for nlm
 // coefficients and nlm + kInject recurrence factors.
 __device__ __forceinline__ void small_legendre(double2* buf, double2* qg, double* be, const SmallArgs& sa,
                                                const DevPlan& D, long field, int lgK, int nt)
@@ -617,12 +618,11 @@ __device__ __forceinline__ void small_legendre(double2* buf, double2* qg, double
         const int m = e / npair, pair = e - m * npair;
         const int nj = L - m + 1, base = m * (2 * L + 1 - m) / 2 + m;
         const double x = D.xp[pair];
-        const int jst = D.inj_j[e];  // a multiple of kInject, nj or more if the lane never starts
         const double2 y = *(const double2*)(D.inj_y + 2 * (size_t)e);
         const int* segexp = D.segexp + D.segoff[m];
         double ua = y.x, ub = y.y, er = 0.0, ei = 0.0, orr = 0.0, oi = 0.0;
-        for (int j = jst; j < nj; j += kInject) {
-            if (j > jst && (j & (kSegLen - 1)) == 0) {
+        for (int j = 0; j < nj; j += kInject) {
+            if (j > 0 && (j & (kSegLen - 1)) == 0) {
                 const int sh = segexp[j / kSegLen];
                 ua = __builtin_amdgcn_ldexp(ua, sh);
                 ub = __builtin_amdgcn_ldexp(ub, sh);
@@ -699,25 +699,22 @@ __device__ __forceinline__ void small_analysis(const double2* buf, const double*
     for (int m = threadIdx.x / G; m <= M; m += nt / G) {
         const int nj = L - m + 1, base = m * (2 * L + 1 - m) / 2 + m;
         const size_t e = (size_t)m * npair + pc;
-        const int jst = act ? D.inj_j[e] : nj;
         const double2 y = *(const double2*)(D.inj_y + 2 * e);
         const int* segexp = D.segexp + D.segoff[m];
         const double2 vn = buf[at((pc << lgK) + m, rs)], vs = buf[at(((nlat - 1 - pc) << lgK) + m, rs)];
-        const double er = wt * (vn.x + vs.x), ei = wt * (vn.y + vs.y);
-        const double orr = wt * (vn.x - vs.x), oi = wt * (vn.y - vs.y);
+        // (There, lanes past the last pair hold the first one's values with
+        // weight 0: nothing, unless they are infinite or not a number.)
+        auto fold = [&](double n, double s) { return fma(0.0, pair == 0 ? n + s : 0.0, wt * (n + s)); };
+        const double er = fold(vn.x, vs.x), ei = fold(vn.y, vs.y), orr = fold(vn.x, -vs.x), oi = fold(vn.y, -vs.y);
         // the part this lane keeps and the one it hands to its neighbour
         const double ek = odd ? ei : er, es = odd ? er : ei, ok = odd ? oi : orr, os = odd ? orr : oi;
         const double cm = (m == 0 || !sa.adjoint) ? 1.0 : 2.0;
-        double ua = 0.0, ub = 0.0;
+        double ua = act ? y.x : 0.0, ub = act ? y.y : 0.0;
         for (int j = 0; j < nj; j += kInject) {
             if (j > 0 && (j & (kSegLen - 1)) == 0) {
                 const int sh = segexp[j / kSegLen];
                 ua = __builtin_amdgcn_ldexp(ua, sh);
                 ub = __builtin_amdgcn_ldexp(ub, sh);
-            }
-            if (j == jst) {
-                ua = y.x;
-                ub = y.y;
             }
             double v[kInject];
 #pragma unroll

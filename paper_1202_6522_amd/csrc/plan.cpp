@@ -217,6 +217,7 @@ void lane_starts(Plan& p)
     p.nck = nck;
     p.blk_first.assign((size_t)(M + 1) * nb, 0);
     p.ck_mask.assign((size_t)(M + 1) * nck * 2, 0u);
+    p.late_starts = std::any_of(p.inj_j.begin(), p.inj_j.end(), [](int j) { return j > 0; });
     for (int m = 0; m <= M; m++) {
         const int nj = p.L - m + 1;
         unsigned* ck = &p.ck_mask[(size_t)m * nck * 2];

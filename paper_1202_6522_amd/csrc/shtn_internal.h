@@ -201,6 +201,7 @@ struct Plan {
     std::vector<double> start_y;              // (M+1) x npair: P_m^m mantissa (host emulation only)
     std::vector<int> start_k;                 // its scaled exponent
     std::vector<int> inj_j;                   // (M+1) x npair: lane start step
+    bool late_starts = false;                 // some lane starts past its order's first degree
     std::vector<double> inj_y;                // (M+1) x npair x 2: state entering it
     std::vector<int> segexp, segoff;
     std::vector<double> rst_y;
