@@ -333,14 +333,15 @@ int check_vec_call(shtn_plan_t plan, const void* a, const void* b, Data kin, con
 }
 
 // Both stages of a scalar call in one launch (k_small_synth, k_small_analys):
-// plans without a set tiling whose fields fit a workgroup and whose latitudes
-// take part in every degree.  (A raised polar threshold drops terms, by the
+// plans without a set tiling whose fields fit a workgroup, with orders so short
+// that it is the faster way, and whose latitudes take part in every degree.  (A raised polar threshold drops terms, by the
 // lane or by the wave according to the kernel: the same for finite data, but
 // not where the dropped input is infinite or not a number.  With the default
 // threshold no plan of this size drops any.)
-bool one_launch(const Plan& p)
+bool one_launch(const Plan& p, int nfields, bool synth)
 {
-    return p.tiling.auto_fw && !p.late_starts && small_fits(p.M, p.nlat, p.K, p.nlm);
+    return p.tiling.auto_fw && !p.late_starts && small_fits(p.M, p.nlat, p.K, p.nlm) &&
+           small_pays(p.L, p.M, p.nlat, p.K, nfields, synth);
 }
 
 // Legendre synthesis-type pass (synthesis or adjoint of the analysis) then c2r.
@@ -350,7 +351,7 @@ int to_grid(shtn_plan_t plan, const double* Q, double* grid, int nfields, void* 
     int rc = check_call(plan, Q, Data::spec, grid, Data::grid, nfields, work);
     if (rc) return rc;
     const Plan& p = *plan->p;
-    if (one_launch(p) && !stored_synth(p.algo)) {
+    if (!stored_synth(p.algo) && one_launch(p, nfields, true)) {
         ProfScope ps(PK_LEG_SYNTH, stream);
         const int e = launch_small_synth(fft_launch(p, nullptr, grid, nfields, 1.0), p.M, p.nlat, p.nlm, Q, adjoint, stream);
         return e ? hip_fail(e, "small synthesis launch") : SHTN_OK;
@@ -368,7 +369,7 @@ int to_spec(shtn_plan_t plan, const double* grid, double* Q, int nfields, void* 
     if (rc) return rc;
     const Plan& p = *plan->p;
     if ((rc = check_analys_stage(p))) return rc;
-    if (one_launch(p) && !stored_analys(p.algo)) {
+    if (!stored_analys(p.algo) && one_launch(p, nfields, false)) {
         ProfScope ps(PK_LEG_ANALYS, stream);
         const FftLaunch l = fft_launch(p, grid, nullptr, nfields, adjoint ? 1.0 : 2.0 * 3.14159265358979323846 / p.nphi);
         const int e = launch_small_analys(l, p.M, p.nlat, p.nlm, Q, adjoint, stream);

@@ -578,7 +578,7 @@ __device__ __forceinline__ void move_f(double2* buf, const double* Fin, double* 
 // 5.8 and 7.2 on the GPU, against 10.5 and 10.4, 6.1 and 7.2; 512 fields 8.7 and
 // 10.5 on the GPU against 15.5 and 26.1.  Beyond one lane per (order, pair) of
 // the workgroup the GPU's time is longer than that of two launches (lmax 36,
-// synthesis: 8.7 against 7.5).
+// synthesis: 8.7 against 7.5), and so it is for long orders (small_pays).
 // ---------------------------------------------------------------------------
 struct SmallArgs {
     const double* q;   // synthesis: spectra
@@ -1204,12 +1204,38 @@ bool small_fits(int M, int nlat, int K, long nlm)
            (M + 1) * ((nlat + 1) / 2) <= kSmallThreads;
 }
 
+static int small_threads(int M, int nlat, int K)
+{
+    const int lanes = (M + 1) * ((nlat + 1) / 2), pts = nlat * K;
+    return std::min(kSmallThreads, (std::max(lanes, (pts + 7) / 8) + 63) / 64 * 64);
+}
+
+// The one launch takes as long as its longest lane, which runs whole orders,
+// eight degrees at a time (in the analysis the orders that its lane group has
+// in turn; groups of 32 lanes take half as long again per eight degrees),
+// where the two launches cut orders into pieces and fill the chip.  Six times
+// eight degrees for few fields; twice that from 256 fields on, which are bound
+// by work and not by latency.  GPU us, one launch and two: synthesis, one field,
+// lmax 47 and 63 of 16 orders 6.7 and 6.7, 7.7 and 6.9, 512 fields at lmax 127
+// 14.6 and 18.6; analysis, one field, lmax 31 of 32 and of 8 orders 7.3 and 7.5,
+// 8.8 and 6.9 (in a sequence of calls the host's 10.5 us for two launches and
+// 8.0 for one decide), lmax 127 of 8 orders 16.4 and 7.1, of one at lmax 2000
+// 184 and 10; 512 fields at lmax 47 of 8 orders 12.7 and 12.5.
+bool small_pays(int L, int M, int nlat, int K, int nfields, bool synth)
+{
+    const int npair = (nlat + 1) / 2, most = nfields >= 256 ? 24 : 12;
+    if (synth) return 2 * ((L + 8) / 8) <= most;
+    const int lanes = npair <= 16 ? 16 : 32, groups = small_threads(M, nlat, K) / lanes;
+    int steps = 0;
+    for (int m = 0; m <= M; m += groups) steps += (L - m + 8) / 8;
+    return (lanes == 16 ? 2 : 3) * steps <= most;
+}
+
 template <bool SYNTH>
 static int launch_small(const FftLaunch& l, int M, int nlat, long nlm, const SmallArgs& sa, void* stream)
 {
-    const int lanes = (M + 1) * ((nlat + 1) / 2), pts = nlat * l.K;
-    const int nt = std::min(kSmallThreads, (std::max(lanes, (pts + 7) / 8) + 63) / 64 * 64);
-    const size_t lds = small_lds_bytes(pts, l.K, nlm);
+    const int nt = small_threads(M, nlat, l.K);
+    const size_t lds = small_lds_bytes(nlat * l.K, l.K, nlm);
 #define SHTN_SMALL(LGK)                                                                                            \
     if (l.K == 1 << LGK) {                                                                                         \
         if (SYNTH)                                                                                                 \

@@ -435,6 +435,7 @@ int launch_r2c(const FftLaunch& a, void* stream);
 // Both stages of a synthesis or analysis in one launch, for plans so small that
 // a field fits one workgroup (fft.hip); q: spectra.
 bool small_fits(int M, int nlat, int K, long nlm);
+bool small_pays(int L, int M, int nlat, int K, int nfields, bool synth);
 int launch_small_analys(const FftLaunch& l, int M, int nlat, long nlm, double* q, int adjoint, void* stream);
 int launch_small_synth(const FftLaunch& l, int M, int nlat, long nlm, const double* q, int adjoint, void* stream);
 
