@@ -305,7 +305,7 @@ __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
         } else {
             const int jc = (c - js0) & ~(kMfChunk - 1);  // first degree of the chunk, from js0
 #pragma unroll
-            for (int v = 0; v < NV; v++) acc[wid][((c - js0 - jc) / kOct * NV + v) * 64 + lane] = val[v];
+            for (int v = 0; v < NV; v++) acc[wv][((c - js0 - jc) / kOct * NV + v) * 64 + lane] = val[v];
             if (cn >= j1 || (cn - js0) % kMfChunk == 0) {
                 // add up the waves' sums, wave by wave an octet each
                 __syncthreads();
@@ -338,7 +338,7 @@ __global__ void __launch_bounds__(64 * W, 2) k_legendre_analys_mf(LegArgs a)
                 if constexpr (W > 1) {
                     // (the workgroup is past its last chunk's sums)
 #pragma unroll
-                    for (int v = 0; v < NV; v++) acc[wid][v * 64 + lane] = val[v];
+                    for (int v = 0; v < NV; v++) acc[wv][v * 64 + lane] = val[v];
                     __syncthreads();
 #pragma unroll
                     for (int v = 0; v < NV; v++) {

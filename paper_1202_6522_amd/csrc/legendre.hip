@@ -753,7 +753,8 @@ __device__ __forceinline__ void analys_unit(
                 }
             } else {
                 const int jc = (c - SC - js0) & ~(kWideChunk - 1);  // first degree of the chunk, from js0
-                if (h == 0) acc[wid][((j_out - js0 - jc) * FW + f_out) * 2 + comp] = sum;
+                // (by latitudes: the order of the sum is the same for every unit)
+                if (h == 0) acc[wv][((j_out - js0 - jc) * FW + f_out) * 2 + comp] = sum;
                 if (c >= j1 || (c - js0) % kWideChunk == 0) {
                     // the chunk's last pass is in: add up the waves' sums
                     __syncthreads();
