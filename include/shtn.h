@@ -171,7 +171,8 @@ long shtn_plan_table(shtn_plan_t plan, int which, void* dst, size_t bytes);
  * call); m_pairing (synthesis units: 0 longest first, 1 long and short units
  * alternating); split (analysis n-range piece length, a
  * multiple of 32; 0 = automatic); fft_rows (latitude rows per FFT workgroup,
- * 0 = automatic: four, or eight of fewer than 256 longitudes).  Rebuilds the unit lists and restart tables:
+ * 0 = automatic: four, or eight of fewer than 256
+ * longitudes, and more of fewer than 64 in calls of very many rows).  Rebuilds the unit lists and restart tables:
  * re-upload afterwards.  Returns SHTN_EINVAL for unsupported values. */
 int shtn_plan_set_tiling(shtn_plan_t plan, int synth_lp, int analys_lp, int analys_waves, int fw,
                          int m_pairing, int split, int fft_rows);

@@ -54,10 +54,10 @@ void plan_ranges(const Plan& p, std::vector<Range>& r)
                      p.ptab.head_bytes + (size_t)p.ptab.nblocks * 256 * sizeof(double), false});
 }
 
-int rows_per_block(const Plan& p)
+int rows_per_block(const Plan& p, int nfields)
 {
     const int cap = fft_rows_cap(p.K);  // rows of K points that fill the largest workgroup
-    int r = p.tiling.fft_rows > 0 ? p.tiling.fft_rows : fft_rows_auto(p.K);
+    int r = p.tiling.fft_rows > 0 ? p.tiling.fft_rows : fft_rows_auto(p.K, p.nlat, nfields);
     if (r > cap) r = cap;
     if (r > p.nlat) r = p.nlat;
     return r;
@@ -187,7 +187,7 @@ FftLaunch fft_launch(const Plan& p, const double* in, double* out, int nfields, 
 {
     FftLaunch f{};
     f.plans = dplan(p);
-    f.rows_per_block = rows_per_block(p);
+    f.rows_per_block = rows_per_block(p, nfields);
     f.nblocks = (p.nlat + f.rows_per_block - 1) / f.rows_per_block;
     f.points = f.rows_per_block * p.K;
     f.grid_y = nfields;
@@ -561,7 +561,7 @@ long shtn_plan_table(shtn_plan_t plan, int which, void* dst, size_t bytes)
     const void* src = nullptr;
     size_t n = 0;
     int tiling[9] = {p.tiling.synth_lp, p.tiling.analys_lp, p.tiling.fw, p.tiling.m_pairing,
-                     p.split_used, rows_per_block(p), p.tiling.analys_waves, kInject, p.polar_log2};
+                     p.split_used, rows_per_block(p, 1), p.tiling.analys_waves, kInject, p.polar_log2};
     switch (which) {
     case 0: src = p.xp.data(); n = p.xp.size() * 8; break;
     case 1: src = p.sp.data(); n = p.sp.size() * 8; break;

@@ -272,14 +272,17 @@ void build_tables(shtn_batch_s& b, const BatchTiling& t)
     // ---- FFT row blocks: {slot, plan, first row, rows} ----
     b.fft_kmax = 1;
     b.fft_points = 1;
-    for (auto* p : b.plans) {
-        b.fft_kmax = std::max(b.fft_kmax, p->K);
-        b.fft_points = std::max(b.fft_points, rows_per_block(*p) * p->K);
+    std::vector<int> rows;  // per plan
+    for (size_t pi = 0; pi < b.plans.size(); pi++) {
+        const Plan& p = *b.plans[pi];
+        rows.push_back(rows_per_block(p, std::max(1, range[pi].second - range[pi].first)));
+        b.fft_kmax = std::max(b.fft_kmax, p.K);
+        b.fft_points = std::max(b.fft_points, rows.back() * p.K);
     }
     b.rowblocks.clear();
     for (int s = 0; s < ns; s++) {
         const Plan& p = *b.plans[b.slot_plan[s]];
-        const int rpb = rows_per_block(p);
+        const int rpb = rows[b.slot_plan[s]];
         for (int r0 = 0; r0 < p.nlat; r0 += rpb) {
             int rb[4] = {s, b.slot_plan[s], r0, std::min(rpb, p.nlat - r0)};
             b.rowblocks.insert(b.rowblocks.end(), rb, rb + 4);

@@ -1110,7 +1110,20 @@ int fft_rows_cap(int K) { return K <= kFftPoints ? kFftPoints / K : 1; }
 // and 8.1; lmax 63, 64 rows 12.6 and 10.2, 8 rows 6.8 and 7.1.  Sixteen fields
 // at lmax 511: 8 rows 29.8 and 36.6, 4 rows 29.8 and 29.0, 2 rows 35.4 and
 // 33.6.
-int fft_rows_auto(int K) { return K >= 128 ? 4 : 8; }
+// Short rows (eight of fewer than 64 points leave most of a wave without points)
+// in great number, above 16 workgroups per CU, are bound by the workgroups and
+// not by latency: as many rows, by powers of two, as bring them down to that
+// number, up to a full wave of eight points per lane.  262,144 rows, c2r and r2c
+// in us, with eight rows and by this rule: of 2 longitudes 33.7 and 39.7, 11.1
+// and 13.2; of 8 38.1 and 43.9, 14.1 and 15.3; of 16 33.0 and 35.9, 16.6 and
+// 17.3; of 32 36.4 and 45.3, 30.8 and 30.7; of 64 (not taken) 50.9 and 50.7, 55.1
+// and 49.6.
+int fft_rows_auto(int K, int nlat, int nfields)
+{
+    int rows = K >= 128 ? 4 : 8;
+    while (K <= 16 && 2 * rows * K <= 512 && rows < nlat && (long)nfields * ((nlat + rows - 1) / rows) > 4096) rows *= 2;
+    return rows;
+}
 
 // Threads of a launch whose largest block holds `points` complex points: one
 // per P points, whole waves.

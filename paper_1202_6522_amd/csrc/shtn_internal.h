@@ -254,7 +254,7 @@ enum class Data { spec, grid };
 // and, when built, its stored-P table.
 void plan_ranges(const Plan& p, std::vector<Range>& r);
 int hip_error(int e, const char* where);
-int rows_per_block(const Plan& p);  // FFT rows per workgroup for a plan
+int rows_per_block(const Plan& p, int nfields);  // FFT rows per workgroup for a call of so many fields
 
 // Host plan construction (plan.cpp).
 Plan* build_plan(int L, int M, int nlat, int nphi, std::string& err);
@@ -430,7 +430,7 @@ struct FftLaunch {
 };
 int launch_c2r(const FftLaunch& a, void* stream);
 int fft_rows_cap(int K);     // rows of K complex points held by one FFT workgroup
-int fft_rows_auto(int K);    // rows per workgroup unless the caller sets them
+int fft_rows_auto(int K, int nlat, int nfields);  // rows per workgroup unless the caller sets them
 int launch_r2c(const FftLaunch& a, void* stream);
 // Both stages of a synthesis or analysis in one launch, for plans so small that
 // a field fits one workgroup (fft.hip); q: spectra.
