@@ -175,6 +175,7 @@ int leg_to_f(const Plan& p, const double* Q, double* F, int nfields, int adjoint
     l.nfields = nfields;
     l.adjoint = adjoint;
     l.top = top;
+    l.rotate = p.M < 64;
     {
         ProfScope ps(PK_LEG_SYNTH, stream);
         e = launch_legendre_synth(l, stream);

@@ -147,7 +147,12 @@ __device__ __forceinline__ void synth_tail(SynthState<LP, FW>& s, const double (
 // workgroups is therefore taken backwards, so that a CU gets long and short
 // units in turn.  (At lmax 1023 the work of the SIMDs then spreads by 1.2%;
 // taken forwards throughout by 16%, and the kernel ended with the busiest,
-// 45.8 us against 37.3.)
+// 45.8 us against 37.3.)  Orders are dealt to the queues in turn, so those of a
+// plan with few orders differ much in length; its field groups then go from
+// queue to queue, each XCD taking every order for some of the fields.  (256
+// fields at lmax 4000, synthesis with its FFT: of one order 1,440 -> 470
+// us, of nine 2,953 -> 2,080; the recurrence tables of 64 orders still lie in
+// each XCD's L2.)
 constexpr int kSynthWaves = 4;
 constexpr int kXcdCus = 32;
 
@@ -160,7 +165,7 @@ __device__ __forceinline__ bool synth_unit(const LegArgs& a, int wave, int& unit
     const int p = w * a.waves + wave;
     const int s = p / a.groups;
     group = a.group0 + p - s * a.groups;
-    unit = s * kXcds + x;
+    unit = s * kXcds + (a.rotate ? (x + group) % kXcds : x);
     return unit < a.nunits;
 }
 
@@ -803,7 +808,8 @@ static int launch_synth_t(const LegLaunch& l, void* stream)
         // two waves per SIMD or fewer: one per workgroup (lmax 255, one
         // field: 10.2 us, with four 11.2; lmax 511: 16.2, with four 17.9)
         const int waves = (long)l.nunits * ng > 2048 ? kSynthWaves : 1;
-        LegArgs a{l.plans, l.units, l.q_off, l.f_off, l.in, l.out, l.nfields, l.adjoint, l.nunits, ng, g0, waves, l.top};
+        LegArgs a{l.plans, l.units, l.q_off, l.f_off, l.in, l.out, l.nfields, l.adjoint, l.nunits, ng, g0, waves, l.top,
+                  l.rotate};
         const int per_xcd = (l.nunits / kXcds * ng + waves - 1) / waves;
         hipLaunchKernelGGL((k_legendre_synth<LP, FW, VEC>), dim3(kXcds * per_xcd), dim3(64 * waves), 0,
                            (hipStream_t)stream, a);

@@ -47,6 +47,7 @@ struct LegArgs {
     // vector transforms: per (field, order) the coefficient of x P_L (synthesis),
     // or the sum with x P_L (analysis), at 2 (f (M+1) + m)
     double* top = nullptr;
+    int rotate = 0;  // synthesis: a unit's field groups go to the XCDs in turn (see synth_unit)
 };
 
 __device__ __forceinline__ long field_q_off(const LegArgs& a, int f, long nlm)

@@ -348,6 +348,7 @@ struct LegLaunch {
     int lp, fw;            // template selection
     int waves = 1;         // analysis: waves per unit (latitude pairs 64 lp waves)
     double* top = nullptr; // vector transforms: the terms with x P_L (see vector.hip), else null
+    int rotate = 0;        // synthesis: a unit's field groups go to the XCDs in turn (see synth_unit)
 };
 // Stored-P kernels (ptable.hip).
 struct PtabArgs {
