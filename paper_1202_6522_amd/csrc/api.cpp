@@ -275,8 +275,10 @@ int f_to_leg(const Plan& p, const double* F, double* Q, int nfields, int adjoint
             l.units = dev_table_int(p, TB_SHORT_UNITS);
             l.nunits = (int)(p.short_units.size() / kUnitInts);
         };
-        if (const int mf = top ? mf_vec_fields(p.npair, nfields)
-                               : (p.tiling.auto_fw ? mf_fields(p.npair, p.nlm, nfields) : 0)) {
+        const int mf = top ? mf_vec_fields(p.npair, nfields)
+                           : (p.tiling.auto_fw ? mf_fields(p.npair, p.nlm, (long)(p.mf_units[0].size() / kUnitInts), nfields)
+                                               : 0);
+        if (mf) {
             // the longest pieces that still give two waves for each of the
             // 2048 slots: a unit's set-up costs as much as some 40 degrees
             const long groups = (nfields + mf - 1) / mf;

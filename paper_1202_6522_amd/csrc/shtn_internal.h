@@ -380,6 +380,13 @@ int launch_vec_spec_out(const DevPlan* plan, int L, int M, const double* A4, dou
                         int nn, void* stream);
 int launch_legendre_synth(const LegLaunch& a, void* stream);
 int launch_legendre_analys(const LegLaunch& a, void* stream);
+// Waves of a unit (each covers 256 latitude pairs with up to four fields, 128 with eight).
+inline int mf_waves(int npair, int fields)
+{
+    int w = 1;
+    while ((fields == 8 ? 128 : 256) * w < npair) w *= 2;
+    return w;
+}
 // Several fields of one plan with the sums on the matrix cores (analys_mf.hip).
 // Fields per unit: 8, 4, or 0 where the vector kernel is the better one.  A
 // unit of eight fields costs about as much as 6.1 fields in the vector kernel,
@@ -387,12 +394,20 @@ int launch_legendre_analys(const LegLaunch& a, void* stream);
 // against 348, 4 fields 152 against 178, 3 fields 148 against 136), and small
 // calls are bound by latency (lmax 255: 8 fields 18.8 against 17.7, 16 fields
 // 22.6 against 27.7; lmax 383, 8 fields 41 both).
-inline int mf_fields(int npair, long nlm, int nfields)
+// And a call has to fill the chip: of four fields per unit, or of one group of
+// eight, 1,600 waves for its 2,048 slots (npieces: units of one field; us: lmax
+// 1023 of 41 orders, 4 fields, 1,536 waves, 34.9 against 30.8; lmax 300 of 201
+// orders and 1,000 latitudes, 4 fields, 1,472 waves, 45.1 against 37.9; lmax 450,
+// 4 fields, 1,824 waves, 40.3 against 42.0; two groups of eight at lmax 1023 of
+// 11 orders, 2,048 waves with the padding, 32.4 against 37.6).
+inline int mf_fields(int npair, long nlm, long npieces, int nfields)
 {
     if ((double)nlm * npair * nfields < 6e7) return 0;
     const double vec = nfields, four = (nfields + 3) / 4 * 3.45,
                  eight = npair <= 1024 ? (nfields + 7) / 8 * 6.1 : vec + four;
-    return vec <= four && vec <= eight ? 0 : (eight <= four ? 8 : 4);
+    if (vec <= four && vec <= eight) return 0;
+    const int mf = eight <= four ? 8 : 4, groups = (nfields + mf - 1) / mf;
+    return npieces * groups * mf_waves(npair, mf) < 1600 && (mf == 4 || groups == 1) ? 0 : mf;
 }
 // Fields per unit of a vector analysis of nfields components, which always
 // runs there: one vector field takes a unit of its own two components.
@@ -401,13 +416,6 @@ inline int mf_vec_fields(int npair, int nfields)
     if (nfields == 2) return 2;
     const double four = (nfields + 3) / 4 * 3.45, eight = npair <= 1024 ? (nfields + 7) / 8 * 6.1 : 2 * four;
     return eight <= four ? 8 : 4;
-}
-// Waves of a unit (each covers 256 latitude pairs with up to four fields, 128 with eight).
-inline int mf_waves(int npair, int fields)
-{
-    int w = 1;
-    while ((fields == 8 ? 128 : 256) * w < npair) w *= 2;
-    return w;
 }
 int launch_legendre_analys_mf(const LegLaunch& a, int npair, int fields, void* stream);
 
