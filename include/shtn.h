@@ -166,14 +166,16 @@ long shtn_plan_table(shtn_plan_t plan, int which, void* dst, size_t bytes);
  * ceil(nlat/2); built combinations: waves 1 with lp 1-8, 2 with lp 2-8, 4
  * with lp 4 or 8); fields per synthesis wave fw (1, 2, 4; fw = 4 needs
  * synth_lp <= 2); the analysis takes min(fw, 2) fields per wave when
- * analys_lp <= 4 and analys_waves <= 2, else 1 (a plan that was never given a
- * tiling reports fw 1 and chooses the fields per synthesis wave for each
- * call); m_pairing (synthesis units: 0 longest first, 1 long and short units
- * alternating); split (analysis n-range piece length, a
- * multiple of 32; 0 = automatic); fft_rows (latitude rows per FFT workgroup,
- * 0 = automatic: four, or eight of fewer than 256
- * longitudes, and more of fewer than 64 in calls of very many rows).  Rebuilds the unit lists and restart tables:
- * re-upload afterwards.  Returns SHTN_EINVAL for unsupported values. */
+ * analys_lp <= 4 and analys_waves <= 2, else 1; m_pairing (synthesis units: 0
+ * longest first, 1 long and short units alternating); split (analysis n-range
+ * piece length, a multiple of 32; 0 = automatic); fft_rows (latitude rows per
+ * FFT workgroup, 0 = automatic: four, or eight of fewer than 256 longitudes,
+ * and more of fewer than 64 in calls of very many rows).
+ * A plan that was never given a tiling chooses fields per wave and kernels for
+ * each call; it reports fw 1 and the automatic split and rows of a call of one
+ * field, and setting exactly the seven values it reports goes back to that.
+ * Rebuilds the unit lists and restart tables: re-upload afterwards.  Returns
+ * SHTN_EINVAL for unsupported values. */
 int shtn_plan_set_tiling(shtn_plan_t plan, int synth_lp, int analys_lp, int analys_waves, int fw,
                          int m_pairing, int split, int fft_rows);
 
@@ -279,10 +281,11 @@ int shtn_ptable_release(shtn_plan_t plan);
 /* Work decomposition of the stored-P kernels (per wave): synthesis
  * synth_rt (1, 2, 4) tiles of 16 latitude pairs x synth_ct (1, 2) tiles of 8
  * fields; analysis analys_jt (1, 2, 4) tiles of 16 degrees of each parity x
- * analys_ct (1, 2) tiles of 8 fields.  Reports 4, 2, 4, 2 until set, when both run one tile x synth_ct
- * (analys_ct).  A call of at most 8
- * fields runs with one field tile whatever the setting.  SHTN_EINVAL for
- * other values.  Takes effect at the next call. */
+ * analys_ct (1, 2) tiles of 8 fields.  Until one is set the tiles are chosen
+ * for each call (one tile of pairs or degrees, one to four of fields) and
+ * 4, 2, 4, 2 is reported; setting 4, 2, 4, 2 goes back to that.  A call of at
+ * most 8 fields runs with one field tile whatever the setting.  SHTN_EINVAL
+ * for other values.  Takes effect at the next call. */
 int shtn_ptable_set_tiling(shtn_plan_t plan, int synth_rt, int synth_ct, int analys_jt, int analys_ct);
 /* tiling4 = {synth_rt, synth_ct, analys_jt, analys_ct}. */
 int shtn_ptable_get_tiling(shtn_plan_t plan, int* tiling4);
@@ -364,8 +367,8 @@ int shtn_batch_analys(shtn_batch_t batch, const double* gridpacked, double* Qpac
  * synthesis units in longest-first order, or long and short units
  * alternating; analys_merge (0, 1): 0 launches the Legendre analysis once per
  * latitude-pair class (64, 128, 256, 512 pairs), 1 launches it once with the
- * largest class.  A batch that was never given a tiling reports {1, 1, 0, 0}
- * and chooses the fields per synthesis wave by itself.  Re-upload
+ * largest class.  {1, 1, 0, 0} is the tiling of a batch that was not given
+ * one, which chooses the fields per synthesis wave by itself.  Re-upload
  * afterwards. */
 int shtn_batch_set_tiling(shtn_batch_t batch, int synth_lp, int fw, int m_pairing, int analys_merge);
 /* tiling4 = {synth_lp, fw, m_pairing, analys_merge}. */

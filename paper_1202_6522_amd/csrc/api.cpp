@@ -613,14 +613,20 @@ int shtn_plan_set_tiling(shtn_plan_t plan, int synth_lp, int analys_lp, int anal
     if (split < 0 || split % kSegLen) return fail(SHTN_EINVAL, "split must be a multiple of 32");
     if (fft_rows < 0) return fail(SHTN_EINVAL, "fft_rows must be >= 0");
     Tiling old = p.tiling;
-    p.tiling.synth_lp = synth_lp;
-    p.tiling.analys_lp = analys_lp;
-    p.tiling.analys_waves = analys_waves;
-    p.tiling.fw = fw;
-    p.tiling.auto_fw = false;
-    p.tiling.m_pairing = m_pairing;
-    p.tiling.split = split;
-    p.tiling.fft_rows = fft_rows;
+    p.tiling = automatic_tiling(p);
+    // what a plan without a set tiling reports (shtn_plan_table 13) makes it one again
+    Tiling& t = p.tiling;
+    if (synth_lp != t.synth_lp || analys_lp != t.analys_lp || analys_waves != t.analys_waves || fw != t.fw ||
+        m_pairing != t.m_pairing || split != automatic_split(p.nlm) || fft_rows != rows_per_block(p, 1)) {
+        t.synth_lp = synth_lp;
+        t.analys_lp = analys_lp;
+        t.analys_waves = analys_waves;
+        t.fw = fw;
+        t.auto_fw = false;
+        t.m_pairing = m_pairing;
+        t.split = split;
+        t.fft_rows = fft_rows;
+    }
     return rebuild_tables(p, [&] { p.tiling = old; });
 }
 
@@ -816,7 +822,8 @@ int shtn_ptable_set_tiling(shtn_plan_t plan, int synth_rt, int synth_ct, int ana
     if (!ok_t(synth_rt) || !ok_t(analys_jt)) return fail(SHTN_EINVAL, "synth_rt and analys_jt must be 1, 2 or 4");
     if (!ok_c(synth_ct) || !ok_c(analys_ct)) return fail(SHTN_EINVAL, "synth_ct and analys_ct must be 1 or 2");
     PTable& t = plan->p->ptab;
-    t.auto_tiles = false;
+    // (what is reported until a decomposition is set chooses it per call again)
+    t.auto_tiles = synth_rt == 4 && synth_ct == 2 && analys_jt == 4 && analys_ct == 2;
     t.synth_rt = synth_rt;
     t.synth_ct = synth_ct;
     t.analys_jt = analys_jt;

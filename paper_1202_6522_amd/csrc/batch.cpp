@@ -34,7 +34,7 @@ namespace {
 struct BatchTiling {
     int synth_lp = 1;      // latitude pairs per synthesis lane (block of 64 lp pairs per wave)
     int fw = 1;            // fields per wave (fields of the same plan)
-    bool auto_fw = false;  // no tiling set yet: the synthesis takes as many as suit the batch
+    bool auto_fw = false;  // the synthesis takes as many as suit the batch
     int m_pairing = 0;     // synthesis unit order: 1 = long and short units alternate
     int analys_merge = 0;  // analysis: 1 = a single launch at the largest pairs-per-lane class
     int stored = 0;        // 1 = plans with a current stored-P table use the stored kernels
@@ -92,6 +92,14 @@ struct shtn_batch_s {
 };
 
 namespace {
+
+// The tiling with these values.  {1, 1, 0, 0} is the one of a batch that was not
+// given any, whose synthesis chooses the fields per wave.
+BatchTiling make_tiling(int synth_lp, int fw, int m_pairing, int analys_merge, int stored)
+{
+    const bool automatic = synth_lp == 1 && fw == 1 && !m_pairing && !analys_merge;
+    return BatchTiling{synth_lp, fw, automatic, m_pairing, analys_merge, stored};
+}
 
 // A synthesis unit's set-up next to its degrees (one of 40 degrees takes about
 // twice as long as one of none).  Without it, one queue took nearly all the
@@ -618,7 +626,7 @@ bool cache_lookup(const char* path, const std::string& key, BatchTiling& t)
         if (is >> c.synth_lp >> c.fw >> c.m_pairing >> c.analys_merge) {
             if (!(is >> c.stored)) c.stored = 0;
             if (validate(c) != SHTN_OK) continue;
-            t = c;
+            t = make_tiling(c.synth_lp, c.fw, c.m_pairing, c.analys_merge, c.stored);
             return true;
         }
     }
@@ -696,7 +704,7 @@ shtn_batch_t shtn_batch(int nfields, const shtn_plan_t* plans)
         so += 2 * (size_t)kTablePad;  // block loads may run past the last field
         b->work_total_bytes = align256((fo + so) * 8);
         b->max_image = image_bound(*b);
-        b->tiling.auto_fw = true;
+        b->tiling = make_tiling(1, 1, 0, 0, 0);
         build_tables(*b, b->tiling);
         return b;
     } catch (const std::bad_alloc&) {
@@ -755,7 +763,7 @@ int shtn_batch_analys(shtn_batch_t batch, const double* gridpacked, double* Qpac
 int shtn_batch_set_tiling(shtn_batch_t batch, int synth_lp, int fw, int m_pairing, int analys_merge)
 {
     if (!batch) return set_error(SHTN_EINVAL, "null batch");
-    BatchTiling t{synth_lp, fw, false, m_pairing, analys_merge, batch->tiling.stored};
+    const BatchTiling t = make_tiling(synth_lp, fw, m_pairing, analys_merge, batch->tiling.stored);
     int rc = validate(t);
     if (rc) return rc;
     try {
@@ -851,7 +859,7 @@ int shtn_batch_tune(shtn_batch_t batch, const double* Qpacked, double* gridpacke
             for (int lp : {1, 2})
                 for (int fw : {1, 2, 4})
                     for (int mp : {0, 1})
-                        for (int merge : {0, 1}) cands.push_back(BatchTiling{lp, fw, false, mp, merge, st});
+                        for (int merge : {0, 1}) cands.push_back(make_tiling(lp, fw, mp, merge, st));
         for (const BatchTiling& t : cands) {
             build_tables(b, t);
             b.tiling = t;

@@ -351,12 +351,7 @@ Plan* build_plan(int L, int M, int nlat, int nphi, std::string& err)
         p->rtw[2 * m + 1] = (double)sinl(a);
     }
 
-    // default tiling: one pair per synthesis lane, two where the waves are
-    // many (lmax 1023: 41.6 us with one pair, 43.0 with two; lmax 2047: 244.0
-    // and 235.5); one analysis wave covers every pair of its order
-    p->tiling.synth_lp = (long)(M + 1) * ((np + 63) / 64) >= 24576 ? 2 : 1;
-    p->tiling.m_pairing = 0;
-    analys_shape(np, p->tiling.analys_lp, p->tiling.analys_waves);
+    p->tiling = automatic_tiling(*p);
     if (rebuild_units(*p, err)) { delete p; return nullptr; }
     build_image(*p);
     ptable_layout(*p);
@@ -471,6 +466,24 @@ void pack_synth_queues(std::vector<SynthUnit> (&q)[kXcds], int alternate, std::v
         }
 }
 
+int automatic_split(long nlm)
+{
+    // about two pieces per SIMD at large sizes (256 at lmax 1023)
+    const long target = nlm / 2048;
+    return (int)std::max<long>(64, (target / kSegLen) * kSegLen);
+}
+
+Tiling automatic_tiling(const Plan& p)
+{
+    // one pair per synthesis lane, two where the waves are many (lmax 1023: 41.6
+    // us with one pair, 43.0 with two; lmax 2047: 244.0 and 235.5); one analysis
+    // wave covers every pair of its order
+    Tiling t;
+    t.synth_lp = (long)(p.M + 1) * ((p.npair + 63) / 64) >= 24576 ? 2 : 1;
+    analys_shape(p.npair, t.analys_lp, t.analys_waves);
+    return t;
+}
+
 int rebuild_units(Plan& p, std::string& err)
 {
     const Tiling& t = p.tiling;
@@ -506,11 +519,7 @@ int rebuild_units(Plan& p, std::string& err)
     // next piece to the first free slot, so the short ones fill the tail),
     // and the shorter XCD queues are padded with units without work.
     int S = t.split;
-    if (S <= 0) {
-        // about two pieces per SIMD at large sizes (256 at lmax 1023)
-        const long target = p.nlm / 2048;
-        S = (int)std::max<long>(64, (target / kSegLen) * kSegLen);
-    }
+    if (S <= 0) S = automatic_split(p.nlm);
     if (S % kSegLen) { err = "split must be a multiple of 32"; return -1; }
     p.split_used = S;
     // (pieces longer than the longest order are the same as one of its length)

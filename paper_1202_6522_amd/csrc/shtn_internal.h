@@ -156,7 +156,7 @@ struct Tiling {
     int analys_lp = 8;
     int analys_waves = 1;  // waves per analysis unit
     int fw = 1;         // fields per wave
-    bool auto_fw = true;  // no tiling set yet: the fields per synthesis wave are chosen per call (synth_fw)
+    bool auto_fw = true;  // no tiling set: fields per wave and kernels are chosen per call
     int m_pairing = 0;  // synthesis: 1 = long and short units alternate in the launch order
     int split = 0;     // analysis: pieces of this many degrees, 0 = automatic
     int fft_rows = 0;  // latitude rows per FFT workgroup, 0 = automatic
@@ -258,6 +258,9 @@ int rows_per_block(const Plan& p, int nfields);  // FFT rows per workgroup for a
 
 // Host plan construction (plan.cpp).
 Plan* build_plan(int L, int M, int nlat, int nphi, std::string& err);
+// Tiling of a plan that was not given one, and its degrees per analysis piece.
+Tiling automatic_tiling(const Plan& p);
+int automatic_split(long nlm);
 int rebuild_units(Plan& p, std::string& err);     // units + restart states for the tiling
 void lane_starts(Plan& p);                        // start step and state of every (order, pair) lane
 // First / last start step of the lanes [i0, i1) of order m that start in

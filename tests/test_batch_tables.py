@@ -88,7 +88,7 @@ def main(stub_path):
     size = S.shtn_batch_device_bytes(batch)
     S.shtn_plan_set_tiling(plan, 1, 4, 1, 1, 0, 32, 1)
     S.shtn_plan_upload(plan, 1 << 40, None)
-    S.shtn_batch_set_tiling(batch, 1, 1, 0, 0)
+    S.shtn_batch_set_tiling(batch, 1, 1, 1, 0)  # the most units
     copied.value = 0
     rc = S.load_library().shtn_batch_upload(batch, ctypes.c_void_p(1 << 41), None)
     assert rc == S.SHTN_ESTATE and copied.value == 0, (rc, copied.value, size)

@@ -7,6 +7,8 @@ import textwrap
 
 import pytest
 
+from paper_1202_6522_amd import shtn as S
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -32,3 +34,36 @@ def test_pieces_longer_than_any_order(lmax):
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100, preexec_fn=limit,
                        cwd=ROOT)
     assert r.returncode == 0 and "done" in r.stdout, r.stderr[-2000:]
+
+
+@pytest.mark.parametrize("shape", [(7, 7, 8, 16), (255, 255, 256, 512), (300, 40, 2001, 128)])
+def test_setting_what_is_reported_changes_nothing(shape):
+    # the plan goes back to choosing per call, after another tiling too: the
+    # tables that only such a plan holds are there again
+    h, ref = S.shtn_plan(*shape), S.shtn_plan(*shape)
+    size = S.shtn_plan_device_bytes(ref)
+    tables = [S.shtn_plan_table(ref, k).tobytes() for k in (9, 11, 12, 13)]
+    t = [int(v) for v in S.shtn_plan_table(ref, 13)]
+    reported = (t[0], t[1], t[6], t[2], t[3], t[4], t[5])
+    for other in (None, (1, 8, 4, 1, 1, 128, 2), (2, 8, 4, 2, 0, 0, 0)):
+        if other:
+            S.shtn_plan_set_tiling(h, *other)
+            assert S.shtn_plan_device_bytes(h) != size
+        S.shtn_plan_set_tiling(h, *reported)
+        assert S.shtn_plan_device_bytes(h) == size
+        assert [S.shtn_plan_table(h, k).tobytes() for k in (9, 11, 12, 13)] == tables
+    S.shtn_plan_destroy(h)
+    S.shtn_plan_destroy(ref)
+
+
+def test_reported_batch_and_table_tilings():
+    h = S.shtn_plan(40, 40, 41, 128)
+    b = S.shtn_batch([h] * 3)
+    for other in ((2, 4, 1, 0), (1, 1, 0, 0)):
+        S.shtn_batch_set_tiling(b, *other)
+        assert tuple(S.shtn_batch_get_tiling(b)) == other
+    S.shtn_ptable_set_tiling(h, 2, 1, 4, 2)
+    S.shtn_ptable_set_tiling(h, 4, 2, 4, 2)
+    assert S.shtn_ptable_get_tiling(h) == [4, 2, 4, 2]
+    S.shtn_batch_destroy(b)
+    S.shtn_plan_destroy(h)
