@@ -20,7 +20,6 @@ round trips of the same workload on the host cores for at least 10 s.
 from __future__ import annotations
 
 import argparse
-import hashlib
 import json
 import os
 import sys
@@ -33,25 +32,17 @@ PEAK_FP64_TFLOPS = 78.6
 METRIC = "transforms/s & FP64 peak fraction at lmax=1023; batched vs per-field"
 
 
-def _src_hash(path):
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
-
-
-KERNEL_SOURCE = {"legendre_synth": "legendre.hip", "legendre_analys": "legendre.hip", "c2r": "fft.hip", "r2c": "fft.hip"}
-
-
 def _summary(file_name, kernel_name, field):
     """A per-launch figure from a committed counter summary under profiles/,
-    if it was taken on the current source of the kernel; else None."""
+    if it was taken on the current source and headers of the kernel; else None."""
     path = os.path.join(ROOT, "profiles", file_name)
     if not os.path.exists(path):
         return None
     with open(path) as f:
         d = json.load(f)
-    src = os.path.join(ROOT, "paper_1202_6522_amd", "csrc", KERNEL_SOURCE[kernel_name])
+    from paper_1202_6522_amd import counters
     k = d.get(kernel_name)
-    if not k or k.get("source_sha") != _src_hash(src):
+    if not k or k.get("source_sha") != counters.source_hash(k["source"]):
         return None
     return k.get(field)
 

@@ -5,7 +5,8 @@ reads a `rocprofv3 --pmc ... --output-format csv` result of a run of
 `bench.py --scalar-only` and writes, per shtn kernel, the median over its
 dispatches of each FP64 instruction counter and the FP64 floating-point
 operations per launch they imply, tagged with the hash of the kernel's source
-file (bench.py uses a summary only while the source is unchanged).
+file and of the headers it shares (bench.py uses a summary only while they are
+unchanged).
 
 Counting: SQ_INSTS_VALU_{FMA,MUL,ADD,TRANS}_F64 count wave instructions; a
 wave instruction covers 64 lanes, an FMA is two operations, the others one.
@@ -28,26 +29,27 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
-# kernel name prefix -> (summary key, source file)
+# kernel template -> (summary key, source file)
 KERNELS = {
     "shtn::k_legendre_synth": ("legendre_synth", "legendre.hip"),
     "shtn::k_legendre_analys": ("legendre_analys", "legendre.hip"),
+    "shtn::k_legendre_analys_mf": ("legendre_analys_mf", "analys_mf.hip"),
     "shtn::k_c2r": ("c2r", "fft.hip"),
     "shtn::k_r2c": ("r2c", "fft.hip"),
 }
 
 
-def source_hash(name):
-    with open(os.path.join(HERE, "csrc", name), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+def source_hash(name, csrc=os.path.join(HERE, "csrc")):
+    """Hash of a kernel's source file and of the headers beside it."""
+    h = hashlib.sha256()
+    for n in [name] + sorted(f for f in os.listdir(csrc) if f.endswith(".h")):
+        with open(os.path.join(csrc, n), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def kernel_key(name):
-    base = name.replace("void ", "", 1)
-    for prefix, v in KERNELS.items():
-        if base.startswith(prefix):
-            return v
-    return None
+    return KERNELS.get(name.replace("void ", "", 1).split("<")[0].split("(")[0])
 
 
 def medians(path):
