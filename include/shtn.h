@@ -412,7 +412,8 @@ int shtn_batch_tune(shtn_batch_t batch, const double* Qpacked, double* gridpacke
  * recorded events and returns, for one kernel kind, the summed duration in
  * milliseconds and the number of launches since the last reset.  Kinds:
  * 0 (no kernel), 1 Legendre synthesis, 2 Legendre analysis,
- * 3 Fourier synthesis (c2r), 4 Fourier analysis (r2c).  Not for use under
+ * 3 Fourier synthesis (c2r), 4 Fourier analysis (r2c).  Calls of small plans
+ * that run both stages in one launch count under 1 or 2 alone.  Not for use under
  * stream capture.  shtn_profile_select restricts the timing to the kinds
  * whose bit is set in kind_mask (all kinds by default): every event pair
  * costs a few microseconds of GPU time between kernels. */

@@ -91,7 +91,7 @@ int check_call(shtn_plan_t plan, const void* in, Data kin, const void* out, Data
     const Plan& p = *plan->p;
     std::vector<Range> r{{"the input", in, data_bytes(p, kin, nfields), false},
                          {"the output", out, data_bytes(p, kout, nfields), true},
-                         {"the workspace", work, work_layout(p, nfields).total, true}};
+                         {"the workspace", work, work_bytes(p, nfields), true}};
     plan_ranges(p, r);
     return check_disjoint(r);
 }
@@ -298,9 +298,11 @@ int f_to_leg(const Plan& p, const double* F, double* Q, int nfields, int adjoint
 }
 
 // Workspace of the vector transforms of nfields fields: F of the four scalar
-// passes, F of the two components, the four spectra, the rescaled spectra.
+// passes, F of the two components, the four spectra.  (Two passes use half of
+// the first and last; the size keeps the room for four more spectra that it
+// had.)
 struct VecLayout {
-    size_t f4, fv, q4, qs, total;
+    size_t f4, fv, q4, total;
 };
 VecLayout vec_layout(const Plan& p, int nfields)
 {
@@ -309,8 +311,7 @@ VecLayout vec_layout(const Plan& p, int nfields)
     v.f4 = 0;
     v.fv = v.f4 + align256(4 * (size_t)nfields * fs);
     v.q4 = v.fv + align256(2 * (size_t)nfields * fs);
-    v.qs = v.q4 + align256(4 * (size_t)nfields * p.nlm * 16);
-    v.total = v.qs + align256((4 * (size_t)nfields * p.nlm + kTablePad) * 16);
+    v.total = v.q4 + align256(4 * (size_t)nfields * p.nlm * 16) + align256((4 * (size_t)nfields * p.nlm + kTablePad) * 16);
     return v;
 }
 
@@ -503,7 +504,7 @@ int shtn_plan_upload(shtn_plan_t plan, void* dev_buf, void* stream)
 size_t shtn_work_bytes(shtn_plan_t plan, int nfields)
 {
     if (!plan || !plan->p || nfields < 1) return 0;
-    return work_layout(*plan->p, nfields).total;
+    return work_bytes(*plan->p, nfields);
 }
 
 int shtn_synth(shtn_plan_t plan, const double* Q, double* grid, int nfields, void* work, void* stream)

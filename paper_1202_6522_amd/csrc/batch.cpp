@@ -63,9 +63,8 @@ struct shtn_batch_s {
     std::vector<int> slot_field;          // slot -> user field (slots grouped by plan)
     std::vector<int> slot_plan;           // slot -> distinct plan index
     std::vector<size_t> q_off, g_off;     // per user field (+ total), in doubles
-    std::vector<long> slot_q, slot_g, slot_f, slot_s;  // per slot offsets in doubles
-    size_t work_f_doubles = 0, work_total_bytes = 0;
-    long max_nlm = 0;
+    std::vector<long> slot_q, slot_g, slot_f;  // per slot offsets in doubles
+    size_t work_total_bytes = 0;
     BatchTiling tiling;
     int synth_fw = 1;  // fields per synthesis wave of the current unit tables
     // unit tables of the current tiling
@@ -77,8 +76,7 @@ struct shtn_batch_s {
     int fft_kmax = 1;  // longest FFT rows of the batch (sizes the FFT's LDS)
     // device image
     std::vector<unsigned char> image;
-    size_t off_plans = 0, off_slot_plan = 0, off_q = 0, off_g = 0, off_f = 0, off_s = 0,
-           off_su = 0, off_au = 0, off_rb = 0;
+    size_t off_plans = 0, off_q = 0, off_g = 0, off_f = 0, off_su = 0, off_au = 0, off_rb = 0;
     size_t max_image = 0;
     void* dev = nullptr;
     bool uploaded = false;
@@ -303,11 +301,9 @@ void build_tables(shtn_batch_s& b, const BatchTiling& t)
     b.off_plans = off;
     off = align256(off + b.plans.size() * sizeof(DevPlan));
     b.image.resize(off, 0);
-    b.off_slot_plan = off; off = put_vec(b.image, off, b.slot_plan);
     b.off_q = off; off = put_vec(b.image, off, b.slot_q);
     b.off_g = off; off = put_vec(b.image, off, b.slot_g);
     b.off_f = off; off = put_vec(b.image, off, b.slot_f);
-    b.off_s = off; off = put_vec(b.image, off, b.slot_s);
     b.off_su = off; off = put_vec(b.image, off, b.synth_units);
     b.off_au = off; off = put_vec(b.image, off, b.analys_units);
     b.off_rb = off; off = put_vec(b.image, off, b.rowblocks);
@@ -684,24 +680,17 @@ shtn_batch_t shtn_batch(int nfields, const shtn_plan_t* plans)
                     b->slot_field.push_back(f);
                     b->slot_plan.push_back((int)pi);
                 }
-        // workspace: F then the rescaled spectra, per slot, 256-byte aligned
-        size_t fo = 0;
+        // workspace: F per slot, 256-byte aligned (the size keeps the room for a
+        // spectrum per slot that it had)
+        size_t fo = 0, so = 2 * (size_t)kTablePad;
         for (int s = 0; s < nfields; s++) {
             const Plan& p = *b->plans[b->slot_plan[s]];
             b->slot_q.push_back((long)b->q_off[b->slot_field[s]]);
             b->slot_g.push_back((long)b->g_off[b->slot_field[s]]);
             b->slot_f.push_back((long)fo);
             fo += align256((size_t)f_layout(p.M, p.nlat).size * 16) / 8;
-            b->max_nlm = std::max(b->max_nlm, p.nlm);
-        }
-        b->work_f_doubles = fo;
-        size_t so = 0;
-        for (int s = 0; s < nfields; s++) {
-            const Plan& p = *b->plans[b->slot_plan[s]];
-            b->slot_s.push_back((long)so);
             so += align256((size_t)p.nlm * 16) / 8;
         }
-        so += 2 * (size_t)kTablePad;  // block loads may run past the last field
         b->work_total_bytes = align256((fo + so) * 8);
         b->max_image = image_bound(*b);
         b->tiling = make_tiling(1, 1, 0, 0, 0);

@@ -1,7 +1,7 @@
 // Synthesis without a caller workspace and without any allocation
-// (shtn_synth_noalloc, include/shtn.h): the longitude coefficients F and the
-// rescaled spectrum that shtn_synth keeps in its `work` argument live here in
-// one static device array per GPU, loaded with the library's code object.
+// (shtn_synth_noalloc, include/shtn.h): the longitude coefficients F that
+// shtn_synth keeps in its `work` argument live here in one static device array
+// per GPU, loaded with the library's code object.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -53,8 +53,7 @@ extern "C" int shtn_synth_noalloc(shtn_plan_t plan, const double* Q, double* gri
     void* ptr = nullptr;
     int rc = scratch_address(&ptr);
     if (rc) return rc;
-    // Nothing in the workspace needs to start at zero: the kernels write
-    // every entry of F and of the rescaled spectrum they later read, and the
-    // padding behind the spectrum is loaded but never used.
+    // Nothing in the workspace needs to start at zero: the kernels write every
+    // entry of F that they later read.
     return shtn::synth_on_work(plan, Q, grid, nfields, ptr, stream);
 }

@@ -692,13 +692,10 @@ void build_image(Plan& p)
     p.image.resize(off, 0);
 }
 
-WorkLayout work_layout(const Plan& p, int nfields)
+size_t work_bytes(const Plan& p, int nfields)
 {
-    WorkLayout w;
-    w.f_bytes = align256((size_t)nfields * f_layout(p.M, p.nlat).size * 16);
-    w.q_bytes = align256(((size_t)nfields * p.nlm + kTablePad) * 16);  // padded for block loads
-    w.total = w.f_bytes + w.q_bytes;
-    return w;
+    return align256((size_t)nfields * f_layout(p.M, p.nlat).size * 16) +
+           align256(((size_t)nfields * p.nlm + kTablePad) * 16);
 }
 
 }  // namespace shtn

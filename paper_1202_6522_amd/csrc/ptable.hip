@@ -162,7 +162,7 @@ __global__ void __launch_bounds__(64) k_ptable_build(const DevPlan* plan, const 
 // holds D[pair l/16 + 4 r][column l%16], r < 4.  Even and odd degrees accumulate
 // apart; the fold north = E + O, south = E - O is then lane-local.
 //
-// Bound by the table's bytes, read once per 16 fields: 268 MB at lmax 511, 50
+// Bound by the table's bytes, read once per 32 fields: 268 MB at lmax 511, 50
 // us at the rate of a plain read of as much.  The order's coefficients go
 // through LDS once per workgroup instead of through L2 once per wave, and the
 // table past the caches, which it would sweep clear of them.  16 fields at lmax

@@ -300,13 +300,10 @@ constexpr int kXcds = 8;
 void pack_synth_queues(std::vector<SynthUnit> (&q)[kXcds], int alternate, std::vector<int>& units);
 size_t align256(size_t v);
 
-// Workspace layout of a plan call with nfields fields.
-struct WorkLayout {
-    size_t f_bytes;   // F: nfields x f_layout().size complex
-    size_t q_bytes;   // room for nfields spectra (nlm complex each; the scalar transforms do not use it)
-    size_t total;
-};
-WorkLayout work_layout(const Plan& p, int nfields);
+// Workspace bytes of a plan call with nfields fields: F, nfields x f_layout().size
+// complex (and the room for nfields spectra that the size has always had: it
+// decides which calls shtn_synth_noalloc takes).
+size_t work_bytes(const Plan& p, int nfields);
 
 // Fields per wave of the analysis kernel for a (pairs per lane, waves) class:
 // the largest count <= fw among the built kernels (two fields with lp <= 4

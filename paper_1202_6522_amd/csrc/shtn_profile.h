@@ -3,7 +3,7 @@
 
 namespace shtn {
 
-enum ProfKind { PK_PRESCALE = 0, PK_LEG_SYNTH = 1, PK_LEG_ANALYS = 2, PK_C2R = 3, PK_R2C = 4 };
+enum ProfKind { PK_NONE = 0, PK_LEG_SYNTH = 1, PK_LEG_ANALYS = 2, PK_C2R = 3, PK_R2C = 4 };
 constexpr int kProfKinds = 5;
 
 // While set (per thread), ProfScope records nothing: used around stream

@@ -379,6 +379,7 @@ def shtn_batch_tune(h, Q, grid, Qout, work, stream, reps=10, cache_path=None):
     return best.value
 
 
+# (no kernel is of kind 0 any more; small calls in one launch are of the Legendre kinds)
 PROFILE_KINDS = {0: "prescale", 1: "legendre_synth", 2: "legendre_analys", 3: "c2r", 4: "r2c"}
 
 
