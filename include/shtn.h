@@ -228,10 +228,10 @@ int shtn_synth_noalloc(shtn_plan_t plan, const double* Q, double* grid, int nfie
  * analysis is the projection on the basis fields of each (n, m), divided by
  * their squared norm n(n+1): it inverts the synthesis for band-limited
  * fields (nlat >= lmax + 1); degree 0 comes out 0 and Im of m = 0 as 0.
- * Internally four scalar Legendre passes of modified spectra (or of
- * weighted longitude coefficients) with the plan's algorithm, tiling and
- * polar threshold, through sin(theta) dP_n^m/dtheta = n x P_n^m -
- * c_n P_{n-1}^m.  work: shtn_vec_work_bytes(plan, nfields) bytes of device
+ * Internally scalar Legendre passes of modified spectra (or of weighted
+ * longitude coefficients), through sin(theta) dP_n^m/dtheta = n x P_n^m -
+ * c_n P_{n-1}^m, with the plan's algorithm, tiling and polar threshold: two
+ * passes per field on the fly without a set tiling, else four.  work: shtn_vec_work_bytes(plan, nfields) bytes of device
  * memory, 256-byte aligned.  Errors as for shtn_synth; the two outputs may
  * overlap no other buffer of the call (S and T may be one buffer, as may
  * Vtheta and Vphi on input). */
