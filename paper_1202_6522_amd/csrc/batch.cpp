@@ -503,6 +503,8 @@ int upload(shtn_batch_s& b, void* dev_buf, void* stream)
 {
     for (auto* p : b.plans)
         if (!p->uploaded) return set_error(SHTN_ESTATE, "plan of the batch not uploaded");
+    // (until the copy below is done, the host's tables are not the buffer's)
+    b.uploaded = false;
     // unit tables built from an earlier state of a plan (lane starts, tiling,
     // stored-P table): rebuild them for the current one
     if (plan_gens(b) != b.tables_gen) {
@@ -851,6 +853,8 @@ int shtn_batch_tune(shtn_batch_t batch, const double* Qpacked, double* gridpacke
                         for (int merge : {0, 1}) cands.push_back(make_tiling(lp, fw, mp, merge, st));
         for (const BatchTiling& t : cands) {
             build_tables(b, t);
+            // (a plan may have got more units since the batch was made)
+            if (b.image.size() > b.max_image) continue;
             b.tiling = t;
             if ((rc = upload(b, dev, stream))) break;
             if ((rc = capture(b, 0, Qpacked, gridpacked, work))) break;

@@ -18,10 +18,30 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HIP_STUB = r"""
 #include <stddef.h>
 size_t copied;
-int hipMemcpyAsync(void* dst, const void* src, size_t n, int kind, void* stream) { copied = n; return 0; }
-int hipStreamSynchronize(void* stream) { return 0; }
+static int handle;
+int hipMemcpyAsync(void* dst, const void* src, size_t n, int kind, void* stream)
+{
+    if (n > copied) copied = n;
+    return 0;
+}
 int hipLaunchKernel(const void* f, ...) { return 0; }
+int hipFuncSetAttribute(const void* f, ...) { return 0; }
 int hipGetLastError(void) { return 0; }
+int hipGetDevice(int* d) { *d = 0; return 1; }
+int hipStreamSynchronize(void* s) { return 0; }
+int hipStreamCreateWithFlags(void** s, unsigned f) { *s = &handle; return 0; }
+int hipStreamDestroy(void* s) { return 0; }
+int hipStreamBeginCapture(void* s, int mode) { return 0; }
+int hipStreamEndCapture(void* s, void** g) { *g = &handle; return 0; }
+int hipGraphInstantiate(void** e, void* g, void* a, void* b, size_t n) { *e = &handle; return 0; }
+int hipGraphDestroy(void* g) { return 0; }
+int hipGraphExecDestroy(void* e) { return 0; }
+int hipGraphLaunch(void* e, void* s) { return 0; }
+int hipEventCreate(void** e) { *e = &handle; return 0; }
+int hipEventDestroy(void* e) { return 0; }
+int hipEventRecord(void* e, void* s) { return 0; }
+int hipEventSynchronize(void* e) { return 0; }
+int hipEventElapsedTime(float* ms, void* a, void* b) { static int k; *ms = 1.0f + k++ % 7; return 0; }
 """
 
 # plans (lmax, mmax, nlat, nphi) and how many fields each has
@@ -82,6 +102,24 @@ def main(stub_path):
         for p in plans:
             S.shtn_plan_destroy(p)
     print("largest image over reported size %.3f" % worst)
+    lib = S.load_library()
+
+    def tune(batch, size, at):
+        # the tuner uploads every candidate
+        copied.value = 0
+        us = ctypes.c_float()
+        rc = lib.shtn_batch_tune(batch, *(ctypes.c_void_p(next(at)) for _ in range(4)), None, 1, None, ctypes.byref(us))
+        assert rc == S.SHTN_OK and 0 < copied.value <= size, (rc, copied.value, size)
+
+    for fields in BATCHES:
+        plans = [S.shtn_plan(*shape) for shape, _ in fields]
+        at = itertools.count(1 << 40, 1 << 36)
+        for p in plans:
+            S.shtn_plan_upload(p, next(at), None)
+        batch = S.shtn_batch([p for p, (_, n) in zip(plans, fields) for _ in range(n)])
+        S.shtn_batch_upload(batch, next(at), None)
+        tune(batch, S.shtn_batch_device_bytes(batch), at)
+        S.shtn_batch_destroy(batch)
     # a plan whose tables grew after the batch was made: refused, whatever else changed since
     plan = S.shtn_plan(300, 300, 301, 1024)
     batch = S.shtn_batch([plan] * 40)
@@ -90,8 +128,20 @@ def main(stub_path):
     S.shtn_plan_upload(plan, 1 << 40, None)
     S.shtn_batch_set_tiling(batch, 1, 1, 1, 0)  # the most units
     copied.value = 0
-    rc = S.load_library().shtn_batch_upload(batch, ctypes.c_void_p(1 << 41), None)
+    rc = lib.shtn_batch_upload(batch, ctypes.c_void_p(1 << 41), None)
     assert rc == S.SHTN_ESTATE and copied.value == 0, (rc, copied.value, size)
+    # fits with fewer units; the tuner leaves out the tilings that do not
+    S.shtn_batch_set_tiling(batch, 2, 4, 0, 0)
+    S.shtn_batch_upload(batch, 1 << 41, None)
+    tune(batch, size, itertools.count(1 << 42, 1 << 36))
+    # after a refused upload, calls are refused too: the tables are not those of the buffer
+    S.shtn_batch_upload(batch, 1 << 41, None)
+    S.shtn_plan_set_tiling(plan, 1, 4, 1, 1, 0, 32, 1)
+    S.shtn_plan_upload(plan, 1 << 40, None)
+    S.shtn_batch_set_tiling(batch, 1, 1, 1, 0)
+    q, g, w = (ctypes.c_void_p(k << 43) for k in (1, 2, 3))
+    assert lib.shtn_batch_upload(batch, ctypes.c_void_p(1 << 41), None) == S.SHTN_ESTATE
+    assert lib.shtn_batch_synth(batch, q, g, w, None) == S.SHTN_ESTATE
 
 
 def test_images_fit_the_reported_size(tmp_path):

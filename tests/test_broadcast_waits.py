@@ -79,7 +79,7 @@ def hazards(code):
     return n, bad
 
 
-def test_checker_sees_a_copy_before_a_broadcast():
+def test_a_copy_before_a_broadcast_is_seen():
     good = """
 0000000000000100 <k>:
 \tv_mov_b32_e32 v4, v9       // 000000000100: 00000000
