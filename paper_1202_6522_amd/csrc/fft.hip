@@ -959,7 +959,12 @@ __device__ __forceinline__ void r2c_rows(const FftArgs& a, const DevPlan& D, con
     // (the usual case), each thread computes the outputs X_m it stores,
     // straight from Z in LDS (entry e: order e >> lg, row e & (nrows - 1));
     // otherwise a post-pass writes X over the buffer first.
-    const bool direct = !SMALL && (rb.nrows & (rb.nrows - 1)) == 0 && rb.nrows <= kFTile && (rb.row0 & (rb.nrows - 1)) == 0;
+    // (blocks of one or two rows of 2,048 points and more always are such a run,
+    // and fill their threads: known to the compiler, whose branches at every
+    // output made these rows 2 to 5% slower)
+    constexpr bool one_or_two = LGK >= 11;
+    const bool direct = one_or_two || (!SMALL && (rb.nrows & (rb.nrows - 1)) == 0 && rb.nrows <= kFTile &&
+                                       (rb.row0 & (rb.nrows - 1)) == 0);
     const int lgr = __builtin_ctz(rb.nrows);
     const int nout = rb.nrows * (M + 1);
     // w^m of this thread's outputs for the post-pass.  Rows of 64 or more
@@ -969,7 +974,7 @@ __device__ __forceinline__ void r2c_rows(const FftArgs& a, const DevPlan& D, con
     // factors are read when they are used (they would cost registers that the
     // usual case needs).  Shorter rows: all are requested here.
     constexpr bool late = LGK >= 6;
-    const bool halves = late && direct && nt * P == npts;
+    const bool halves = one_or_two || (late && direct && nt * P == npts);
     const int hK = K > 1 ? K >> 1 : 1;
     auto factor = [&](int m) {  // w^m, m < K
         const double2 w = ld2(rtw, m < hK ? m : m - hK);
